@@ -54,8 +54,9 @@
  * (dh <= 128); dh is padded inside the library to a multiple of 16;
  * 1 <= chunk <= 512 (the paper's C = 512), forward and backward; a chunk
  * longer than the kernels' token tile (64 rows, 32 at d = 128) runs as
- * consecutive tiles that all take gradients and outputs at the chunk-start
- * weights; e2ttt_apply takes d <= 64; T >= 1 with
+ * tiles that all take gradients and outputs at the chunk-start weights (one
+ * after the other, or, where that is faster, all at once by plain launches
+ * per chunk); e2ttt_apply takes d <= 64; T >= 1 with
  * a ragged last chunk of T mod chunk tokens allowed (Prop. 1 holds for any
  * chunk length).
  * bf16 tensors use MFMA bf16 operands with fp32 accumulation and fp32 state;

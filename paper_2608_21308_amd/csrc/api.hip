@@ -4,11 +4,13 @@
 
 #include <algorithm>
 #include <climits>
+#include <cmath>
 #include <cstdlib>
 
 #include "e2ttt.h"
 #include "e2ttt_internal.h"
 #include "pair_xchg.h"
+#include "tile_path.h"
 
 namespace {
 
@@ -52,6 +54,12 @@ struct Plan {
   size_t off_rbar = 0, off_bnx = 0;      // post-chunk normalisation (backward)
   size_t scratch_bytes = 0;
   bool affine = false;
+  // token-tiled path (long chunks): tile_path.h
+  bool tile = false;
+  long copy = 0, wslot = 0, mslot = 0;
+  int ntile_max = 0;
+  size_t off_aop = 0, off_bop = 0, off_wops = 0, off_mops = 0;
+  size_t off_state = 0, off_bstate = 0, off_gops = 0, off_baop = 0, off_bbop = 0;
 };
 
 e2ttt_status select_config(const e2ttt_desc& d, ChainConfig& cfg) {
@@ -96,7 +104,82 @@ e2ttt_status select_config(const e2ttt_desc& d, ChainConfig& cfg) {
   return E2TTT_OK;
 }
 
-e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl) {
+constexpr int kTileRows = 32;   // tokens of a tile of that path
+
+size_t tile_copy_bytes(const e2ttt_desc& d) {
+  return (size_t)(d.fw == E2TTT_FW_GELU_MLP ? 2 : 3) * ((d.dh + 31) / 32 * 32) * d.d * 2;
+}
+
+// Whether the token-tiled path runs the call: chunks of more than one tile of
+// the chain kernels, where an estimate of a forward chunk's time (us) says that
+// it is the faster path by a margin.  The estimates are fitted to both paths'
+// times over 11 nets (head dims 64 and 128, dh 64 to 512), 2 to 128 units and
+// chunks of 64 to 512 tokens; with the margin of 1.2 the path never lost in
+// them, forward or training step, and gained 1.6x in the geometric mean.
+//   chain: a chunk's tiles one after the other, as many units at once as the
+//     device holds workgroups for.  A 64-token tile at head dim 64 takes 9.7 us
+//     (SwiGLU 11.7), a 32-token tile at head dim 128 12 to 16 us (SwiGLU to 20),
+//     growing with the ranks that swap sums.
+//   tiles: two launches (12 us), the state kernel's walk over the tokens, the
+//     state's way through memory, and the work of all tokens, which the whole
+//     device shares.
+// Measured, chain over tiles, forward: head dim 64, dh 256, C = 128: 8 units
+// 1.3, 32 units 1.1, 96 units 0.5; C = 512: 2.8, 2.0, 0.9; head dim 128, dh 512,
+// C = 128: 8 units 1.9, 128 units 1.5, C = 512: 4.9, 2.7.
+bool takes_tiles(const e2ttt_desc& d, const Plan& pl) {
+  const int len = std::min(d.chunk, d.T), rows = 16 * pl.cfg.ntb;
+  if (!pl.cfg.bf || pl.post_norm || len <= rows || !tile_supported(pl.cfg, d.dh)) return false;
+  const double U = (double)pl.U;
+  const int ns = pl.cfg.ns;
+  const bool sw = d.fw == E2TTT_FW_SWIGLU;
+  const double held = ns > 1 ? 256 / ns / 8 * 8 : 256;   // units that run at once (256 CUs)
+  const double tile_us = d.d == 64 ? (sw ? 11.7 : 9.7) : (sw ? 14.0 + 0.7 * ns : 12.0 + 0.5 * ns);
+  const double chain_us = std::ceil(U / held) * ((len + rows - 1) / rows) * tile_us;
+  const double params = (double)(sw ? 3 : 2) * d.d * d.dh;
+  const double tiles_us = 12.0 + 0.017 * len + 3.7e-6 * U * params +
+                          U * len * (0.2e-3 * d.d / 64 +
+                                     // (four waves take whole blocks of 32 columns)
+                                     1.07e-3 * params / 32768 * std::max(1.0, 128.0 / d.dh));
+  return 1.2 * tiles_us < chain_us;
+}
+
+// Layout of the token-tiled path: one operand copy set of W per chunk when
+// saving (the backward reads them), else one.  U units, tok bytes of a
+// per-token fp32 array, chk of a carry array.
+void tile_plan(const e2ttt_desc& d, Plan& pl, size_t tok, size_t chk) {
+  const size_t U = (size_t)pl.U, tokd = tok * d.d;
+  pl.copy = tile_copy_bytes(d);
+  pl.wslot = (long)U * 3 * pl.copy;
+  pl.mslot = (long)U * pl.copy;
+  pl.ntile_max = (std::min(d.chunk, d.T) + kTileRows - 1) / kTileRows;
+  pl.off_state = pl.off_carry + align_up(chk);
+  pl.off_aop = pl.off_state + align_up(U * 4 * pl.copy);   // W and M, fp32
+  pl.off_bop = pl.off_aop + align_up(U * pl.ntile_max * tile_aop_bytes(pl.cfg, false));
+  pl.off_wops = pl.off_bop + align_up(U * pl.ntile_max * tile_bop_bytes(pl.cfg, d.dh, false));
+  pl.ws_bytes = pl.off_wops + align_up(pl.wslot);
+  pl.off_mops = pl.off_wops + align_up((size_t)pl.NC * pl.wslot);
+  pl.off_zk = pl.off_mops + align_up((size_t)pl.NC * pl.mslot);
+  pl.off_rk = pl.off_zk + align_up(tokd);
+  pl.off_zq = pl.off_rk + align_up(tok);
+  pl.off_rq = pl.off_zq + align_up(tokd);
+  pl.ws_bytes_save = pl.off_rq + align_up(tok);
+  pl.off_kwb = 0;
+  pl.off_kmb = align_up(tok);
+  pl.off_carryb = pl.off_kmb + align_up(tok);
+  pl.off_bstate = pl.off_carryb + align_up(tile_state_groups(d.dh) * chk);
+  pl.off_gops = pl.off_bstate + align_up(U * 4 * pl.copy);
+  pl.off_baop = pl.off_gops + align_up(U * 4 * pl.copy);
+  pl.off_bbop = pl.off_baop + align_up(U * pl.ntile_max * tile_aop_bytes(pl.cfg, true));
+  pl.off_zbar = pl.off_bbop + align_up(U * pl.ntile_max * tile_bop_bytes(pl.cfg, d.dh, true));
+  pl.off_apart = pl.off_zbar + (pl.affine ? align_up(tokd) : 0);
+  const long nb = (d.T + kAffineTokBlock - 1) / kAffineTokBlock;
+  pl.scratch_bytes =
+      pl.off_apart + (pl.affine ? align_up(U * nb * 2 * d.d * sizeof(float)) : 0);
+}
+
+// Plan of a descriptor; with chain_only, of the chain kernels also where the
+// token-tiled path would be taken.
+e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool chain_only = false) {
   if (!desc) return E2TTT_ERR_NULL_ARG;
   const e2ttt_desc& d = *desc;
   if (d.B < 1 || d.H < 1 || d.T < 1 || d.d < 1 || d.dh < 1 || d.chunk < 1)
@@ -122,6 +205,15 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl) {
   pl.P = (d.fw == E2TTT_FW_GELU_MLP ? 2L : 3L) * d.d * d.dh;
   const size_t tok = (size_t)U * d.T * sizeof(float);
   const size_t chk = (size_t)U * pl.NC * 3 * sizeof(float);
+  pl.affine = (d.flags & E2TTT_FLAG_LN_AFFINE) != 0;
+  pl.post_norm = (d.flags & E2TTT_FLAG_POST_NORM) != 0;
+  pl.tile = !chain_only && takes_tiles(d, pl);
+  if (pl.tile) {
+    pl.off_km = align_up(tok);
+    pl.off_carry = pl.off_km + align_up(tok);
+    tile_plan(d, pl, tok, chk);
+    return E2TTT_OK;
+  }
   const long ns = pl.cfg.ns;
   pl.npairs = (ns > 1) ? std::min((U + 7) / 8 * 8, kMaxPairs) : 0;
   const size_t sync_b = (ns > 1) ? (size_t)sync_words(pl.npairs, (int)ns) * sizeof(unsigned) : 0;
@@ -140,7 +232,6 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl) {
   pl.w0b = pl.tpc > 1 && pl.cfg.bf && (pl.cfg.fw == E2TTT_FW_SWIGLU || d.d > 64);
   pl.off_ckpt =
       pl.off_w0 + (pl.w0b ? align_up((size_t)nwg * chain_frz_floats(pl.cfg) * sizeof(float)) : 0);
-  pl.post_norm = (d.flags & E2TTT_FLAG_POST_NORM) != 0;
   pl.nrows = (d.fw == E2TTT_FW_GELU_MLP ? 1L : 2L) * d.dh + d.d;
   const size_t ngroups = (size_t)std::max(pl.npairs, 1L);
   pl.off_ntgt = pl.off_ckpt;
@@ -172,7 +263,6 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl) {
   pl.off_zbar =
       pl.off_frz +
       (pl.tpc > 1 ? align_up((size_t)nwg * 2 * chain_frz_floats(pl.cfg) * sizeof(float)) : 0);
-  pl.affine = (d.flags & E2TTT_FLAG_LN_AFFINE) != 0;
   pl.off_apart = pl.off_zbar + (pl.affine ? align_up(tokd) : 0);
   const long nb = (d.T + kAffineTokBlock - 1) / kAffineTokBlock;
   pl.off_rbar =
@@ -283,6 +373,117 @@ template <class Tp> const Tp* at(const void* base, size_t off) {
 
 }  // namespace
 
+namespace e2ttt {
+
+size_t chain_workspace_bytes(const e2ttt_desc* desc) {
+  Plan pl;
+  return make_plan(desc, pl, true) == E2TTT_OK ? pl.ws_bytes : 0;
+}
+
+e2ttt_status run_forward(const e2ttt_desc* desc, bool chain_only, const float* ln_weight,
+                         const float* ln_bias, const void* q, const void* k, const void* v,
+                         const float* eta, const float* beta, const float* gamma,
+                         const float* w_in, const float* m_in, void* out, float* w_out,
+                         float* m_out, void* workspace, size_t workspace_bytes,
+                         int save_for_backward, void* stream) {
+  Plan pl;
+  e2ttt_status st = make_plan(desc, pl, chain_only);
+  if (st != E2TTT_OK) return st;
+  if (!q || !k || !v || !eta || !beta || !w_in || !out || !w_out || !m_out || !workspace)
+    return E2TTT_ERR_NULL_ARG;
+  st = check_affine(pl, ln_weight, ln_bias, false, nullptr, nullptr);
+  if (st != E2TTT_OK) return st;
+  if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(out) || !aligned16(workspace))
+    return E2TTT_ERR_BAD_SHAPE;
+  if (workspace_bytes < (save_for_backward ? pl.ws_bytes_save : pl.ws_bytes))
+    return E2TTT_ERR_WORKSPACE_TOO_SMALL;
+  if (save_for_backward && (w_out == w_in || (m_in && m_out == m_in))) return E2TTT_ERR_BAD_SHAPE;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  float* kw = at<float>(workspace, pl.off_kw);
+  float* km = at<float>(workspace, pl.off_km);
+  float* carry = at<float>(workspace, pl.off_carry);
+  if (pl.tile) {
+    CoeffFwdArgs c{eta, beta, gamma, kw, km, carry, (int)pl.T, desc->chunk, (int)pl.NC,
+                   pl.U * pl.NC, nullptr, 0, averaged(desc)};
+    hipError_t e = launch_coeff_fwd(c, s);
+    if (e != hipSuccess) return E2TTT_ERR_HIP;
+    TileFwdArgs a{};
+    a.q = q; a.k = k; a.v = v;
+    a.kw = kw; a.km = km; a.carry = carry;
+    a.w_in = w_in; a.m_in = m_in;
+    a.state = at<float>(workspace, pl.off_state);
+    a.out = out; a.w_out = w_out; a.m_out = m_out;
+    a.wops = at<char>(workspace, pl.off_wops);
+    a.aops = at<char>(workspace, pl.off_aop);
+    a.bops = at<char>(workspace, pl.off_bop);
+    a.keep = save_for_backward ? 1 : 0;
+    if (save_for_backward) {
+      a.mops = at<char>(workspace, pl.off_mops);
+      a.zk = at<float>(workspace, pl.off_zk);
+      a.rk = at<float>(workspace, pl.off_rk);
+      a.zq = at<float>(workspace, pl.off_zq);
+      a.rq = at<float>(workspace, pl.off_rq);
+    }
+    a.U = pl.U; a.P = pl.P;
+    a.copy = pl.copy; a.wslot = pl.wslot; a.mslot = pl.mslot;
+    a.T = (int)pl.T; a.C = desc->chunk; a.NC = (int)pl.NC; a.dh = desc->dh;
+    a.ntile_max = pl.ntile_max;
+    a.resln = (desc->flags & E2TTT_FLAG_NO_RESIDUAL_LN) ? 0 : 1;
+    a.eps = desc->ln_eps;
+    a.ln_a = ln_weight; a.ln_b = ln_bias;
+    a.H = desc->H;
+    return finish(launch_tile_fwd(pl.cfg, a, s), s);
+  }
+  unsigned* sync = pl.cfg.ns > 1 ? at<unsigned>(workspace, pl.off_sync) : nullptr;
+  const long np = pl.cfg.ns > 1 ? launch_pairs(pl, false) : 0;
+  if (pl.cfg.ns > 1 && np < 8) return E2TTT_ERR_UNSUPPORTED;
+  CoeffFwdArgs c{eta, beta, gamma, kw, km, carry, (int)pl.T, desc->chunk, (int)pl.NC,
+                 pl.U * pl.NC, sync, sync ? sync_words(np, pl.cfg.ns) : 0, averaged(desc)};
+  hipError_t e = launch_coeff_fwd(c, s);
+  if (e != hipSuccess) return E2TTT_ERR_HIP;
+  if (pl.post_norm) {
+    e = launch_norm_targets(w_in, at<float>(workspace, pl.off_ntgt), pl.U, desc->d, desc->dh,
+                            pl.cfg.fw == E2TTT_FW_GELU_MLP ? 2 : 3, pl.P, s);
+    if (e != hipSuccess) return E2TTT_ERR_HIP;
+  }
+  ChainArgs a{};
+  a.U = pl.U;
+  a.q = q; a.k = k; a.v = v;
+  a.w_in = w_in; a.m_in = m_in;
+  a.kw = kw; a.km = km; a.carry = carry;
+  a.out = out; a.w_out = w_out; a.m_out = m_out;
+  a.ckpt = save_for_backward ? at<char>(workspace, pl.off_ckpt) : nullptr;
+  a.ckpt_stride = pl.ckpt_stride;
+  if (save_for_backward) {
+    a.asave = pl.as_stride ? at<char>(workspace, pl.off_as) : nullptr;
+    a.as_stride = pl.as_stride;
+    a.zk = at<float>(workspace, pl.off_zk);
+    a.rk = at<float>(workspace, pl.off_rk);
+    a.zq = at<float>(workspace, pl.off_zq);
+    a.rq = at<float>(workspace, pl.off_rq);
+  }
+  a.xbuf = at<float>(workspace, pl.off_xbuf);
+  a.w0blk = pl.w0b ? at<float>(workspace, pl.off_w0) : nullptr;
+  a.sync = sync;
+  a.npairs = np;
+  a.wait_ticks = wait_ticks();
+  a.T = (int)pl.T; a.C = desc->chunk; a.NC = (int)pl.NC; a.dh = desc->dh; a.P = pl.P;
+  a.resln = (desc->flags & E2TTT_FLAG_NO_RESIDUAL_LN) ? 0 : 1;
+  a.eps = desc->ln_eps;
+  a.ln_a = ln_weight;
+  a.ln_b = ln_bias;
+  a.H = desc->H;
+  a.ckpt_nc = pl.ckpt_nc;
+  if (pl.post_norm) {
+    a.norm_tgt = at<float>(workspace, pl.off_ntgt);
+    a.nxbuf = at<float>(workspace, pl.off_nx);
+    a.norm_pre = save_for_backward ? at<float>(workspace, pl.off_npre) : nullptr;
+  }
+  return finish(launch_chain_fwd(pl.cfg, a, s), s, sync);
+}
+
+}  // namespace e2ttt
+
 extern "C" {
 
 size_t e2ttt_param_count(const e2ttt_desc* desc) {
@@ -375,68 +576,8 @@ e2ttt_status e2ttt_chunk_forward_ln(const e2ttt_desc* desc, const float* ln_weig
                                     const float* gamma, const float* w_in, const float* m_in,
                                     void* out, float* w_out, float* m_out, void* workspace,
                                     size_t workspace_bytes, int save_for_backward, void* stream) {
-  Plan pl;
-  e2ttt_status st = make_plan(desc, pl);
-  if (st != E2TTT_OK) return st;
-  if (!q || !k || !v || !eta || !beta || !w_in || !out || !w_out || !m_out || !workspace)
-    return E2TTT_ERR_NULL_ARG;
-  st = check_affine(pl, ln_weight, ln_bias, false, nullptr, nullptr);
-  if (st != E2TTT_OK) return st;
-  if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(out) || !aligned16(workspace))
-    return E2TTT_ERR_BAD_SHAPE;
-  if (workspace_bytes < (save_for_backward ? pl.ws_bytes_save : pl.ws_bytes))
-    return E2TTT_ERR_WORKSPACE_TOO_SMALL;
-  if (save_for_backward && (w_out == w_in || (m_in && m_out == m_in))) return E2TTT_ERR_BAD_SHAPE;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  float* kw = at<float>(workspace, pl.off_kw);
-  float* km = at<float>(workspace, pl.off_km);
-  float* carry = at<float>(workspace, pl.off_carry);
-  unsigned* sync = pl.cfg.ns > 1 ? at<unsigned>(workspace, pl.off_sync) : nullptr;
-  const long np = pl.cfg.ns > 1 ? launch_pairs(pl, false) : 0;
-  if (pl.cfg.ns > 1 && np < 8) return E2TTT_ERR_UNSUPPORTED;
-  CoeffFwdArgs c{eta, beta, gamma, kw, km, carry, (int)pl.T, desc->chunk, (int)pl.NC,
-                 pl.U * pl.NC, sync, sync ? sync_words(np, pl.cfg.ns) : 0, averaged(desc)};
-  hipError_t e = launch_coeff_fwd(c, s);
-  if (e != hipSuccess) return E2TTT_ERR_HIP;
-  if (pl.post_norm) {
-    e = launch_norm_targets(w_in, at<float>(workspace, pl.off_ntgt), pl.U, desc->d, desc->dh,
-                            pl.cfg.fw == E2TTT_FW_GELU_MLP ? 2 : 3, pl.P, s);
-    if (e != hipSuccess) return E2TTT_ERR_HIP;
-  }
-  ChainArgs a{};
-  a.U = pl.U;
-  a.q = q; a.k = k; a.v = v;
-  a.w_in = w_in; a.m_in = m_in;
-  a.kw = kw; a.km = km; a.carry = carry;
-  a.out = out; a.w_out = w_out; a.m_out = m_out;
-  a.ckpt = save_for_backward ? at<char>(workspace, pl.off_ckpt) : nullptr;
-  a.ckpt_stride = pl.ckpt_stride;
-  if (save_for_backward) {
-    a.asave = pl.as_stride ? at<char>(workspace, pl.off_as) : nullptr;
-    a.as_stride = pl.as_stride;
-    a.zk = at<float>(workspace, pl.off_zk);
-    a.rk = at<float>(workspace, pl.off_rk);
-    a.zq = at<float>(workspace, pl.off_zq);
-    a.rq = at<float>(workspace, pl.off_rq);
-  }
-  a.xbuf = at<float>(workspace, pl.off_xbuf);
-  a.w0blk = pl.w0b ? at<float>(workspace, pl.off_w0) : nullptr;
-  a.sync = sync;
-  a.npairs = np;
-  a.wait_ticks = wait_ticks();
-  a.T = (int)pl.T; a.C = desc->chunk; a.NC = (int)pl.NC; a.dh = desc->dh; a.P = pl.P;
-  a.resln = (desc->flags & E2TTT_FLAG_NO_RESIDUAL_LN) ? 0 : 1;
-  a.eps = desc->ln_eps;
-  a.ln_a = ln_weight;
-  a.ln_b = ln_bias;
-  a.H = desc->H;
-  a.ckpt_nc = pl.ckpt_nc;
-  if (pl.post_norm) {
-    a.norm_tgt = at<float>(workspace, pl.off_ntgt);
-    a.nxbuf = at<float>(workspace, pl.off_nx);
-    a.norm_pre = save_for_backward ? at<float>(workspace, pl.off_npre) : nullptr;
-  }
-  return finish(launch_chain_fwd(pl.cfg, a, s), s, sync);
+  return run_forward(desc, false, ln_weight, ln_bias, q, k, v, eta, beta, gamma, w_in, m_in, out,
+                     w_out, m_out, workspace, workspace_bytes, save_for_backward, stream);
 }
 
 e2ttt_status e2ttt_chunk_backward(const e2ttt_desc* desc, const void* q, const void* k,
@@ -478,6 +619,50 @@ e2ttt_status e2ttt_chunk_backward_ln(const e2ttt_desc* desc, const float* ln_wei
   if (workspace_bytes < pl.ws_bytes_save || scratch_bytes < pl.scratch_bytes)
     return E2TTT_ERR_WORKSPACE_TOO_SMALL;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  if (pl.tile) {
+    TileBwdArgs a{};
+    a.q = q; a.k = k; a.v = v; a.d_out = d_out;
+    a.kw = at<float>(workspace, pl.off_kw);
+    a.km = at<float>(workspace, pl.off_km);
+    a.carry = at<float>(workspace, pl.off_carry);
+    a.wops = at<char>(workspace, pl.off_wops);
+    a.mops = at<char>(workspace, pl.off_mops);
+    a.zk = at<float>(workspace, pl.off_zk);
+    a.rk = at<float>(workspace, pl.off_rk);
+    a.zq = at<float>(workspace, pl.off_zq);
+    a.rq = at<float>(workspace, pl.off_rq);
+    a.d_w_out = d_w_out; a.d_m_out = d_m_out;
+    a.state = at<float>(scratch, pl.off_bstate);
+    a.d_w_in = d_w_in; a.d_m_in = d_m_in;
+    a.dq = dq; a.dk = dk; a.dv = dv;
+    a.kwb = at<float>(scratch, pl.off_kwb);
+    a.kmb = at<float>(scratch, pl.off_kmb);
+    a.carryb = at<float>(scratch, pl.off_carryb);
+    a.gops = at<char>(scratch, pl.off_gops);
+    a.aops = at<char>(scratch, pl.off_baop);
+    a.bops = at<char>(scratch, pl.off_bbop);
+    a.ln_zbar = pl.affine ? at<float>(scratch, pl.off_zbar) : nullptr;
+    a.U = pl.U; a.P = pl.P;
+    a.copy = pl.copy; a.wslot = pl.wslot; a.mslot = pl.mslot;
+    a.T = (int)pl.T; a.C = desc->chunk; a.NC = (int)pl.NC; a.dh = desc->dh;
+    a.ntile_max = pl.ntile_max;
+    a.resln = (desc->flags & E2TTT_FLAG_NO_RESIDUAL_LN) ? 0 : 1;
+    a.ln_a = ln_weight; a.ln_b = ln_bias;
+    a.H = desc->H;
+    hipError_t e = launch_tile_bwd(pl.cfg, a, s);
+    if (e != hipSuccess) return E2TTT_ERR_HIP;
+    CoeffBwdArgs cb{eta, beta, gamma, a.kwb, a.kmb, a.carryb, d_eta, d_beta, d_gamma,
+                    (int)pl.T, desc->chunk, (int)pl.NC, pl.U * pl.NC, 1,
+                    tile_state_groups(desc->dh), pl.U * pl.T, pl.U * pl.NC * 3, averaged(desc)};
+    e = launch_coeff_bwd(cb, s);
+    if (e == hipSuccess && pl.affine) {
+      AffineGradArgs g{d_out, k, v, a.zk, a.zq, a.ln_zbar, ln_weight, ln_bias,
+                       at<float>(scratch, pl.off_apart), d_ln_weight, d_ln_bias, pl.U, desc->H,
+                       (int)pl.T, desc->d, pl.cfg.bf};
+      e = launch_affine_grad(g, s);
+    }
+    return finish(e, s);
+  }
   unsigned* sync = pl.cfg.ns > 1 ? at<unsigned>(scratch, pl.off_bsync) : nullptr;
   const long np = pl.cfg.ns > 1 ? launch_pairs(pl, true) : 0;
   if (pl.cfg.ns > 1 && np < 8) return E2TTT_ERR_UNSUPPORTED;
@@ -526,7 +711,7 @@ e2ttt_status e2ttt_chunk_backward_ln(const e2ttt_desc* desc, const float* ln_wei
   hipError_t e = launch_chain_bwd(pl.cfg, a, s);
   if (e != hipSuccess) return E2TTT_ERR_HIP;
   CoeffBwdArgs cb{eta, beta, gamma, a.kwb, a.kmb, a.carryb, d_eta, d_beta, d_gamma,
-                  (int)pl.T, desc->chunk, (int)pl.NC, pl.U * pl.NC, pl.cfg.ns,
+                  (int)pl.T, desc->chunk, (int)pl.NC, pl.U * pl.NC, pl.cfg.ns, pl.cfg.ns,
                   pl.U * pl.T, pl.U * pl.NC * 3, averaged(desc)};
   e = launch_coeff_bwd(cb, s);
   if (e == hipSuccess && pl.affine) {
@@ -546,7 +731,7 @@ e2ttt_status e2ttt_wait_status(const e2ttt_desc* desc, const void* workspace,
   if (!workspace && !scratch) return E2TTT_ERR_NULL_ARG;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (hipStreamSynchronize(s) != hipSuccess) return E2TTT_ERR_HIP;
-  if (pl.cfg.ns == 1) return E2TTT_OK;   // one workgroup per unit: no waits
+  if (pl.cfg.ns == 1 || pl.tile) return E2TTT_OK;   // no waits between workgroups
   unsigned word[2] = {0u, 0u};
   if (workspace && hipMemcpy(&word[0], at<unsigned>(workspace, pl.off_sync), sizeof(unsigned),
                              hipMemcpyDeviceToHost) != hipSuccess)

@@ -336,7 +336,8 @@ __device__ void coeff_bwd_long(const CoeffBwdArgs& a, long wid, long base, int l
   }
 }
 
-// LONGC: chunks longer than one wave's 64 tokens (a separate instantiation,
+// LONGC: chunks longer than one wave's 64 tokens, or more than kMaxSlots carry
+// partials (a separate instantiation,
 // so that the short-chunk kernel keeps its small register footprint).
 template <bool LONGC>
 __global__ void __launch_bounds__(256) coeff_bwd_kernel(CoeffBwdArgs a) {
@@ -352,17 +353,18 @@ __global__ void __launch_bounds__(256) coeff_bwd_kernel(CoeffBwdArgs a) {
   // the chain kernel leaves one partial per workgroup of a unit; sum them
   float kwb, kmb, cwb = 0.0f, cmb = 0.0f, cbb = 0.0f;
   sum_slots(a, valid ? base + lane : base, valid, kwb, kmb);
-  float cv[kMaxSlots][3];
+  constexpr int NCS = LONGC ? 2 * kMaxSlots : kMaxSlots;   // token-tiled path: up to 16
+  float cv[NCS][3];
 #pragma unroll
-  for (int sl = 0; sl < kMaxSlots; ++sl) {
-    const long o = (long)min(sl, a.ns - 1) * a.chk_slot + wid * 3;
+  for (int sl = 0; sl < NCS; ++sl) {
+    const long o = (long)min(sl, a.ncs - 1) * a.chk_slot + wid * 3;
     cv[sl][0] = a.carryb[o];
     cv[sl][1] = a.carryb[o + 1];
     cv[sl][2] = a.carryb[o + 2];
   }
 #pragma unroll
-  for (int sl = 0; sl < kMaxSlots; ++sl) {
-    if (sl < a.ns) {
+  for (int sl = 0; sl < NCS; ++sl) {
+    if (sl < a.ncs) {
       cwb += cv[sl][0];
       cmb += cv[sl][1];
       cbb += cv[sl][2];
@@ -436,9 +438,11 @@ hipError_t launch_coeff_fwd(const CoeffFwdArgs& a, hipStream_t stream) {
 }
 
 hipError_t launch_coeff_bwd(const CoeffBwdArgs& a, hipStream_t stream) {
-  if (a.ns < 1 || a.ns > kMaxSlots) return hipErrorInvalidValue;
+  if (a.ns < 1 || a.ns > kMaxSlots || a.ncs < 1 ||
+      a.ncs > 2 * kMaxSlots)
+    return hipErrorInvalidValue;
   const unsigned blocks = (unsigned)((a.nwork + 3) / 4);
-  if (a.C > 64)
+  if (a.C > 64 || a.ncs > kMaxSlots)
     hipLaunchKernelGGL(coeff_bwd_kernel<true>, dim3(blocks), dim3(256), 0, stream, a);
   else
     hipLaunchKernelGGL(coeff_bwd_kernel<false>, dim3(blocks), dim3(256), 0, stream, a);

@@ -5,7 +5,20 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "e2ttt.h"
+
 namespace e2ttt {
+
+// e2ttt_chunk_forward_ln; with chain_only on the chain kernels whatever the
+// chunk length, in a workspace of chain_workspace_bytes.
+e2ttt_status run_forward(const e2ttt_desc* desc, bool chain_only, const float* ln_weight,
+                         const float* ln_bias, const void* q, const void* k, const void* v,
+                         const float* eta, const float* beta, const float* gamma,
+                         const float* w_in, const float* m_in, void* out, float* w_out,
+                         float* m_out, void* workspace, size_t workspace_bytes,
+                         int save_for_backward, void* stream);
+// Workspace of that call without saving (0 for a bad descriptor).
+size_t chain_workspace_bytes(const e2ttt_desc* desc);
 
 struct CoeffFwdArgs {
   const float* eta;
@@ -33,7 +46,8 @@ struct CoeffBwdArgs {
   float* d_gamma;       // nullable iff gamma is
   int T, C, NC;
   long nwork;
-  int ns;               // partial slots of kwb, kmb, carryb (one per workgroup of a unit)
+  int ns;               // partial slots of kwb, kmb (one per workgroup of a unit)
+  int ncs;              // partial slots of carryb
   long tok_slot;        // elements between slots of kwb / kmb (U T)
   long chk_slot;        // elements between slots of carryb (U NC 3)
   int averaged;         // as CoeffFwdArgs::averaged

@@ -17,6 +17,7 @@
 #include <mutex>
 
 #include "e2ttt.h"
+#include "e2ttt_internal.h"
 
 static __device__ __align__(256) unsigned char scratch[E2TTT_STATIC_WORKSPACE_BYTES];
 
@@ -51,9 +52,12 @@ extern "C" e2ttt_status e2ttt_chunk_forward_static(const e2ttt_desc* desc, const
   if (need == 0)   // a bad descriptor: the forward reports which check failed
     return e2ttt_chunk_forward(desc, q, k, v, eta, beta, gamma, w_in, m_in, out, w_out, m_out,
                                nullptr, 0, 0, stream);
-  if (need > E2TTT_STATIC_WORKSPACE_BYTES) return E2TTT_ERR_WORKSPACE_TOO_SMALL;
+  // long chunks whose token-tiled path needs more run on the chain kernels
+  const bool chain = need > E2TTT_STATIC_WORKSPACE_BYTES;
+  if (chain && e2ttt::chain_workspace_bytes(desc) > E2TTT_STATIC_WORKSPACE_BYTES)
+    return E2TTT_ERR_WORKSPACE_TOO_SMALL;
   void* ws = scratch_on_current_device();
   if (!ws) return E2TTT_ERR_HIP;
-  return e2ttt_chunk_forward(desc, q, k, v, eta, beta, gamma, w_in, m_in, out, w_out, m_out, ws,
-                             E2TTT_STATIC_WORKSPACE_BYTES, 0, stream);
+  return e2ttt::run_forward(desc, chain, nullptr, nullptr, q, k, v, eta, beta, gamma, w_in, m_in,
+                            out, w_out, m_out, ws, E2TTT_STATIC_WORKSPACE_BYTES, 0, stream);
 }
