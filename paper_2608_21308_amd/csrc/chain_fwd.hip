@@ -841,17 +841,11 @@ int max_blocks_per_cu() {
 
 template <class S, bool LONG, bool PN>
 hipError_t launch_as(const ChainArgs& a, hipStream_t stream) {
-  if constexpr (S::NS == 1) {
-    hipLaunchKernelGGL((chain_fwd_kernel<S, LONG, PN>), dim3((unsigned)a.U), dim3(S::NT), 0, stream,
-                       a);
-    return hipGetLastError();
-  } else {
-    ChainArgs b = a;
-    void* args[] = {&b};
-    return hipLaunchCooperativeKernel((const void*)chain_fwd_kernel<S, LONG, PN>,
-                                      dim3((unsigned)(S::NS * a.npairs)), dim3(S::NT), args, 0,
-                                      stream);
-  }
+  // (several workgroups per unit: why a plain launch will do is in pair_xchg.h)
+  const long blocks = S::NS == 1 ? a.U : S::NS * a.npairs;
+  hipLaunchKernelGGL((chain_fwd_kernel<S, LONG, PN>), dim3((unsigned)blocks), dim3(S::NT), 0, stream,
+                     a);
+  return hipGetLastError();
 }
 
 template <class S>
