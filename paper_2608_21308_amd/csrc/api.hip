@@ -110,8 +110,7 @@ size_t tile_copy_bytes(const e2ttt_desc& d) {
   return (size_t)(d.fw == E2TTT_FW_GELU_MLP ? 2 : 3) * ((d.dh + 31) / 32 * 32) * d.d * 2;
 }
 
-// Whether the token-tiled path runs the call: chunks of more than one tile of
-// the chain kernels, where an estimate of a forward chunk's time (us) says that
+// Whether the token-tiled path runs the call: chunks of more than 64 tokens, where an estimate of a forward chunk's time (us) says that
 // it is the faster path by a margin.  The estimates are fitted to both paths'
 // times over 11 nets (head dims 64 and 128, dh 64 to 512), 2 to 128 units and
 // chunks of 64 to 512 tokens; with the margin of 1.2 the path never lost in
@@ -128,7 +127,9 @@ size_t tile_copy_bytes(const e2ttt_desc& d) {
 // C = 128: 8 units 1.9, 128 units 1.5, C = 512: 4.9, 2.7.
 bool takes_tiles(const e2ttt_desc& d, const Plan& pl) {
   const int len = std::min(d.chunk, d.T), rows = 16 * pl.cfg.ntb;
-  if (!pl.cfg.bf || pl.post_norm || len <= rows || !tile_supported(pl.cfg, d.dh)) return false;
+  // (at head dim 128 chunks of 33 to 64 tokens gained 1.0x to 1.3x and their
+  // saved operand copies, one set per chunk, took half as much memory again)
+  if (!pl.cfg.bf || pl.post_norm || len <= 64 || !tile_supported(pl.cfg, d.dh)) return false;
   const double U = (double)pl.U;
   const int ns = pl.cfg.ns;
   const bool sw = d.fw == E2TTT_FW_SWIGLU;
