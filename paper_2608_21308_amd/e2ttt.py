@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes
 import os
 from dataclasses import dataclass
+from functools import cached_property
 
 import torch
 
@@ -124,6 +125,19 @@ class Config:
         return Desc(self.B, self.H, self.T, self.d, self.dh, self.chunk, self.fw, self.io,
                     self.flags, self.ln_eps)
 
+    @cached_property
+    def _call(self):
+        """What every call derives from the (frozen) fields: the descriptor by
+        reference, the io type, and the element counts of the token, gate,
+        state and head arrays."""
+        n_tok = self.B * self.H * self.T
+        return (ctypes.byref(self.desc()), self.torch_io, n_tok * self.d, n_tok,
+                self.B * self.H * self.P, self.H * self.d)
+
+    def __getstate__(self):
+        # (a reference to a descriptor is of this process)
+        return {n: v for n, v in self.__dict__.items() if n != "_call"}
+
     @property
     def P(self) -> int:
         return (2 if self.fw == FW_MLP else 3) * self.d * self.dh
@@ -138,11 +152,32 @@ class Config:
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current stream of the current device, as torch.cuda.current_stream() gives it
+    return _raw_stream(_current_device())
+
+
+try:
+    _raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+except AttributeError:   # a build without those bindings
+    def _raw_stream(device):
+        return torch.cuda.current_stream(device).cuda_stream
+
+    _current_device = torch.cuda.current_device
+
+
+def _ok(t, dtype, n, device):
+    """The checks of _check_tensors for one tensor (None passes) at the price
+    a call of a few microseconds can afford; a tensor that fails is then looked
+    at by _check_tensors, which says what is wrong with it."""
+    return t is None or (type(t) in _TENSORS and t.dtype is dtype and t.numel() == n and
+                         t.is_cuda and t.get_device() == device and t.is_contiguous())
+
+
+_TENSORS = (torch.Tensor, torch.nn.Parameter)
 
 
 def _check(st: int, where: str):
@@ -190,13 +225,11 @@ def _check_tensors(cfg: Config, **ts):
 
 
 def workspace_bytes(cfg: Config, save_for_backward: bool) -> int:
-    d = cfg.desc()
-    return int(load().e2ttt_workspace_bytes(ctypes.byref(d), int(bool(save_for_backward))))
+    return int(load().e2ttt_workspace_bytes(cfg._call[0], int(bool(save_for_backward))))
 
 
 def backward_scratch_bytes(cfg: Config) -> int:
-    d = cfg.desc()
-    return int(load().e2ttt_backward_scratch_bytes(ctypes.byref(d)))
+    return int(load().e2ttt_backward_scratch_bytes(cfg._call[0]))
 
 
 def alloc_workspace(cfg: Config, save_for_backward: bool, device="cuda"):
@@ -210,9 +243,19 @@ def forward(cfg: Config, q, k, v, eta, beta, gamma, w_in, m_in=None, *, out=None
             m_out=None, workspace=None, save_for_backward=False, ln_weight=None, ln_bias=None):
     """Runs e2ttt_chunk_forward (e2ttt_chunk_forward_ln with the LayerNorm affine
     ln_weight, ln_bias [H, d]) on the current stream; returns (out, w_out, m_out, workspace)."""
-    _check_tensors(cfg, q=q, k=k, v=v, eta=eta, beta=beta, gamma=gamma, w_in=w_in, m_in=m_in,
-                   out=out, w_out=w_out, m_out=m_out, workspace=workspace, ln_weight=ln_weight,
-                   ln_bias=ln_bias)
+    d, io, n_io, n_gate, n_state, n_head = cfg._call
+    f32 = torch.float32
+    dev = q.get_device() if isinstance(q, torch.Tensor) else -1
+    if not (dev >= 0 and q is not None and _ok(q, io, n_io, dev) and _ok(k, io, n_io, dev) and
+            _ok(v, io, n_io, dev) and _ok(out, io, n_io, dev) and _ok(eta, f32, n_gate, dev) and
+            _ok(beta, f32, n_gate, dev) and _ok(gamma, f32, n_gate, dev) and
+            _ok(w_in, f32, n_state, dev) and _ok(m_in, f32, n_state, dev) and
+            _ok(w_out, f32, n_state, dev) and _ok(m_out, f32, n_state, dev) and
+            (workspace is None or _ok(workspace, torch.uint8, workspace.numel(), dev)) and
+            _ok(ln_weight, f32, n_head, dev) and _ok(ln_bias, f32, n_head, dev)):
+        _check_tensors(cfg, q=q, k=k, v=v, eta=eta, beta=beta, gamma=gamma, w_in=w_in, m_in=m_in,
+                       out=out, w_out=w_out, m_out=m_out, workspace=workspace,
+                       ln_weight=ln_weight, ln_bias=ln_bias)
     lib = load()
     dev = q.device
     if out is None:
@@ -223,8 +266,7 @@ def forward(cfg: Config, q, k, v, eta, beta, gamma, w_in, m_in=None, *, out=None
         m_out = torch.empty_like(w_in)
     if workspace is None:
         workspace = alloc_workspace(cfg, save_for_backward, dev)
-    d = cfg.desc()
-    st = lib.e2ttt_chunk_forward_ln(ctypes.byref(d), _ptr(ln_weight), _ptr(ln_bias), _ptr(q),
+    st = lib.e2ttt_chunk_forward_ln(d, _ptr(ln_weight), _ptr(ln_bias), _ptr(q),
                                     _ptr(k), _ptr(v), _ptr(eta), _ptr(beta), _ptr(gamma),
                                     _ptr(w_in), _ptr(m_in), _ptr(out), _ptr(w_out), _ptr(m_out),
                                     _ptr(workspace), workspace.numel(),
@@ -245,8 +287,7 @@ def forward_static(cfg: Config, q, k, v, eta, beta, gamma, w_in, m_in, out, w_ou
             raise ValueError("%s must be given: this entry point allocates nothing" % name)
     _check_tensors(cfg, q=q, k=k, v=v, eta=eta, beta=beta, gamma=gamma, w_in=w_in, m_in=m_in,
                    out=out, w_out=w_out, m_out=m_out)
-    d = cfg.desc()
-    st = load().e2ttt_chunk_forward_static(ctypes.byref(d), _ptr(q), _ptr(k), _ptr(v), _ptr(eta),
+    st = load().e2ttt_chunk_forward_static(cfg._call[0], _ptr(q), _ptr(k), _ptr(v), _ptr(eta),
                                            _ptr(beta), _ptr(gamma), _ptr(w_in), _ptr(m_in),
                                            _ptr(out), _ptr(w_out), _ptr(m_out), _stream())
     _check(st, "e2ttt_chunk_forward_static")
@@ -273,10 +314,9 @@ def backward(cfg: Config, q, k, v, eta, beta, gamma, w_in, m_in, workspace, d_ou
             grads["d_ln_bias"] = torch.empty_like(ln_weight)
     if scratch is None:
         scratch = torch.empty(backward_scratch_bytes(cfg), dtype=torch.uint8, device=dev)
-    d = cfg.desc()
     g = grads
     st = lib.e2ttt_chunk_backward_ln(
-        ctypes.byref(d), _ptr(ln_weight), _ptr(ln_bias), _ptr(q), _ptr(k), _ptr(v), _ptr(eta),
+        cfg._call[0], _ptr(ln_weight), _ptr(ln_bias), _ptr(q), _ptr(k), _ptr(v), _ptr(eta),
         _ptr(beta), _ptr(gamma), _ptr(w_in), _ptr(m_in), _ptr(workspace), workspace.numel(),
         _ptr(d_out), _ptr(d_w_out), _ptr(d_m_out), _ptr(g["dq"]), _ptr(g["dk"]), _ptr(g["dv"]),
         _ptr(g["d_eta"]), _ptr(g["d_beta"]), _ptr(g["d_gamma"]), _ptr(g["d_w_in"]),
@@ -289,12 +329,16 @@ def backward(cfg: Config, q, k, v, eta, beta, gamma, w_in, m_in, workspace, d_ou
 def apply(cfg: Config, q, w, out=None, ln_weight=None, ln_bias=None):
     """Runs e2ttt_apply (e2ttt_apply_ln with the LayerNorm affine): out = f_W(q)
     for the cfg.T tokens of q per unit, all at the state w [B,H,P]."""
-    _check_tensors(cfg, q=q, w_in=w, out=out, ln_weight=ln_weight, ln_bias=ln_bias)
+    d, io, n_io, _, n_state, n_head = cfg._call
+    dev = q.get_device() if isinstance(q, torch.Tensor) else -1
+    if not (dev >= 0 and _ok(q, io, n_io, dev) and _ok(w, torch.float32, n_state, dev) and
+            _ok(out, io, n_io, dev) and _ok(ln_weight, torch.float32, n_head, dev) and
+            _ok(ln_bias, torch.float32, n_head, dev)):
+        _check_tensors(cfg, q=q, w_in=w, out=out, ln_weight=ln_weight, ln_bias=ln_bias)
     lib = load()
     if out is None:
         out = torch.empty_like(q)
-    d = cfg.desc()
-    st = lib.e2ttt_apply_ln(ctypes.byref(d), _ptr(ln_weight), _ptr(ln_bias), _ptr(q), _ptr(w),
+    st = lib.e2ttt_apply_ln(d, _ptr(ln_weight), _ptr(ln_bias), _ptr(q), _ptr(w),
                             _ptr(out), _stream())
     _check(st, "e2ttt_apply")
     return out
@@ -307,8 +351,7 @@ def wait_status(cfg: Config, workspace=None, scratch=None) -> int:
     if workspace is None and scratch is None:
         raise ValueError("give a workspace, a scratch buffer or both")
     _check_tensors(cfg, workspace=workspace, scratch=scratch)
-    d = cfg.desc()
-    return int(load().e2ttt_wait_status(ctypes.byref(d), _ptr(workspace), _ptr(scratch),
+    return int(load().e2ttt_wait_status(cfg._call[0], _ptr(workspace), _ptr(scratch),
                                         _stream()))
 
 
@@ -319,8 +362,7 @@ def chunk_coeffs(cfg: Config, eta, beta, gamma):
     kw = torch.empty_like(eta)
     km = torch.empty_like(eta)
     carry = torch.empty((cfg.B, cfg.H, cfg.n_chunks, 3), dtype=torch.float32, device=eta.device)
-    d = cfg.desc()
-    st = lib.e2ttt_chunk_coeffs(ctypes.byref(d), _ptr(eta), _ptr(beta), _ptr(gamma), _ptr(kw),
+    st = lib.e2ttt_chunk_coeffs(cfg._call[0], _ptr(eta), _ptr(beta), _ptr(gamma), _ptr(kw),
                                 _ptr(km), _ptr(carry), _stream())
     _check(st, "e2ttt_chunk_coeffs")
     return kw, km, carry
@@ -389,11 +431,16 @@ class E2TTTFunction(torch.autograd.Function):
                                         save_for_backward=True)
         ctx.cfg = cfg
         ctx.save_for_backward(q, k, v, eta, beta, gamma, w_in, m_in, ws)
+        # an unused output's gradient arrives as None (the library's NULL) instead
+        # of zeros that would be filled and read
+        ctx.set_materialize_grads(False)
         return out, w_out, m_out
 
     @staticmethod
     def backward(ctx, d_out, d_w_out, d_m_out):
         q, k, v, eta, beta, gamma, w_in, m_in, ws = ctx.saved_tensors
+        if d_out is None:
+            d_out = torch.zeros_like(q)
         g = backward(ctx.cfg, q, k, v, eta, beta, gamma, w_in, m_in, ws, d_out.contiguous(),
                      None if d_w_out is None else d_w_out.contiguous(),
                      None if d_m_out is None else d_m_out.contiguous())
