@@ -56,9 +56,15 @@ struct Plan {
   bool affine = false;
   // token-tiled path (long chunks): tile_path.h
   bool tile = false;
-  long copy = 0, wslot = 0, mslot = 0;
+  long copy = 0, wunit = 0, wslot = 0, mslot = 0;
   int ntile_max = 0;
   size_t off_aop = 0, off_bop = 0, off_wops = 0, off_mops = 0;
+  // chain kernels that leave the query side out
+  bool qoff = false;
+  bool qall = false;      // token-tiled path: the backward's query side ahead
+  int nslot = 0;          // chunks of a launch without saving
+  long copy0 = 0, wunit0 = 0;   // its operand copies without saving
+  size_t off_wops0 = 0, off_qaop = 0, off_qbop = 0;
   size_t off_state = 0, off_bstate = 0, off_gops = 0, off_baop = 0, off_bbop = 0;
 };
 
@@ -150,13 +156,16 @@ bool takes_tiles(const e2ttt_desc& d, const Plan& pl) {
 void tile_plan(const e2ttt_desc& d, Plan& pl, size_t tok, size_t chk) {
   const size_t U = (size_t)pl.U, tokd = tok * d.d;
   pl.copy = tile_copy_bytes(d);
-  pl.wslot = (long)U * 3 * pl.copy;
+  pl.wunit = 3 * pl.copy;
+  pl.wslot = (long)U * pl.wunit;
   pl.mslot = (long)U * pl.copy;
   pl.ntile_max = (std::min(d.chunk, d.T) + kTileRows - 1) / kTileRows;
   pl.off_state = pl.off_carry + align_up(chk);
+  // the query side of all chunks at once where one chunk's tiles leave CUs idle
+  pl.qall = pl.U * pl.ntile_max <= 128;
   pl.off_aop = pl.off_state + align_up(U * 4 * pl.copy);   // W and M, fp32
-  pl.off_bop = pl.off_aop + align_up(U * pl.ntile_max * tile_aop_bytes(pl.cfg, false));
-  pl.off_wops = pl.off_bop + align_up(U * pl.ntile_max * tile_bop_bytes(pl.cfg, d.dh, false));
+  pl.off_bop = pl.off_aop + align_up(U * pl.ntile_max * tile_aop_bytes(pl.cfg, kTileFwd));
+  pl.off_wops = pl.off_bop + align_up(U * pl.ntile_max * tile_bop_bytes(pl.cfg, d.dh, kTileFwd));
   pl.ws_bytes = pl.off_wops + align_up(pl.wslot);
   pl.off_mops = pl.off_wops + align_up((size_t)pl.NC * pl.wslot);
   pl.off_zk = pl.off_mops + align_up((size_t)pl.NC * pl.mslot);
@@ -170,12 +179,35 @@ void tile_plan(const e2ttt_desc& d, Plan& pl, size_t tok, size_t chk) {
   pl.off_bstate = pl.off_carryb + align_up(tile_state_groups(d.dh) * chk);
   pl.off_gops = pl.off_bstate + align_up(U * 4 * pl.copy);
   pl.off_baop = pl.off_gops + align_up(U * 4 * pl.copy);
-  pl.off_bbop = pl.off_baop + align_up(U * pl.ntile_max * tile_aop_bytes(pl.cfg, true));
-  pl.off_zbar = pl.off_bbop + align_up(U * pl.ntile_max * tile_bop_bytes(pl.cfg, d.dh, true));
+  const size_t nt = U * pl.ntile_max, ntq = nt * (pl.qall ? pl.NC : 1);
+  pl.off_bbop = pl.off_baop + align_up(nt * tile_aop_bytes(pl.cfg, kTileBwdKey));
+  pl.off_qaop = pl.off_bbop + align_up(nt * tile_bop_bytes(pl.cfg, d.dh, kTileBwdKey));
+  pl.off_qbop = pl.off_qaop + align_up(ntq * tile_aop_bytes(pl.cfg, kTileBwdQuery));
+  pl.off_zbar = pl.off_qbop + align_up(ntq * tile_bop_bytes(pl.cfg, d.dh, kTileBwdQuery));
   pl.off_apart = pl.off_zbar + (pl.affine ? align_up(tokd) : 0);
   const long nb = (d.T + kAffineTokBlock - 1) / kAffineTokBlock;
   pl.scratch_bytes =
       pl.off_apart + (pl.affine ? align_up(U * nb * 2 * d.d * sizeof(float)) : 0);
+}
+
+// Whether the chain leaves the query side to kernels over all chunks (forward:
+// the net at W_0 for the chunk's q, its LayerNorm and out; backward: dq and the
+// operands of the query's terms of dW_0).  In the chain they cost a fifth of a
+// chunk's time on the few CUs it uses; apart they use the whole device, but W_0
+// goes through memory as operand copies.  Time of the chain alone over this,
+// head dim 64, C = 64 (C = 16 alike), 8 / 32 / 128 chunks:
+//   forward  MLP 256:    8 units 1.11 1.12 1.19, 32 units 1.06 1.05, 64 units 0.99 0.98
+//            MLP 120:    1.13 1.15 1.23, 1.10 1.11, 64 units 1.07 1.05
+//            SwiGLU 172: 1.15 1.10 1.22, 1.11 1.03, 64 units 1.02 0.95
+//            SwiGLU 64:  1.14 1.09 1.22, 1.11 1.05, 64 units 1.07 0.99
+//   training MLP 256:    1.10 1.16, 1.06 1.09, 64 units 0.98 0.99
+//   step     MLP 120:    1.05 1.18 1.18, 1.08 1.14, 64 units 1.04 1.07
+//            SwiGLU 172: 1.14 1.20 1.20, 1.09 1.13, 64 units 1.03 1.03
+// and with 4 chunks 0.96 to 1.07 (the launches).
+bool leaves_query(const e2ttt_desc& d, const Plan& pl) {
+  const bool mlp = d.fw == E2TTT_FW_GELU_MLP;
+  if (!pl.cfg.bf || d.d != 64 || pl.NC < 8) return false;
+  return pl.U <= (mlp && pl.cfg.ns == 1 ? 64 : 32);
 }
 
 // Plan of a descriptor; with chain_only, of the chain kernels also where the
@@ -239,12 +271,32 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool chain_only = false
   pl.off_nx = pl.off_ntgt + (pl.post_norm ? align_up((size_t)U * pl.nrows * sizeof(float)) : 0);
   pl.off_ckpt = pl.off_nx +
                 (pl.post_norm ? align_up(ngroups * ns * 2 * d.d * sizeof(float)) : 0);
-  pl.ws_bytes = pl.off_ckpt;
+  pl.qoff = !chain_only && leaves_query(d, pl);
+  pl.copy = (long)tile_copy_bytes(d);
+  pl.wunit = 3 * pl.copy;
+  pl.wslot = (long)U * pl.wunit;
+  // without saving the query side needs the first layer's R copies and the second
+  // layer's T copy only, of the chunks of one launch: half of all (SwiGLU, with
+  // half as much again per copy, a third), 12 at least, in up to 256 MB (each
+  // further launch costs some 28 us: the chain's start and end, its query sides)
+  const long nmat = d.fw == E2TTT_FW_GELU_MLP ? 2 : 3;
+  pl.copy0 = pl.copy / nmat * (nmat - 1);
+  pl.wunit0 = 2 * pl.copy0 + pl.copy / nmat;
+  const long wslot0 = (long)U * pl.wunit0;
+  pl.ntile_max = (std::min(d.chunk, d.T) + kTileRows - 1) / kTileRows;
+  pl.nslot =
+      (int)std::min(pl.NC, std::max(12L, std::min((pl.NC + nmat - 1) / nmat, (256L << 20) / wslot0)));
+  const long nrun = (pl.NC + pl.nslot - 1) / pl.nslot;
+  pl.nslot = (int)((pl.NC + nrun - 1) / nrun);
+  pl.off_wops0 = pl.off_ckpt;
+  pl.ws_bytes = pl.off_ckpt + (pl.qoff ? align_up((size_t)pl.nslot * wslot0) : 0);
   pl.ckpt_stride = chain_ckpt_bytes(pl.cfg);
   // with the normalisation the backward also reads the final state (one more block)
   pl.ckpt_nc = pl.NC + (pl.post_norm ? 1 : 0);
   const size_t tokd = tok * d.d;
-  pl.off_npre = pl.off_ckpt + align_up((size_t)U * pl.ckpt_nc * ns * 2 * pl.ckpt_stride);
+  // (with the operand copies in memory, checkpoints of M alone)
+  pl.off_npre = pl.off_ckpt +
+                align_up((size_t)U * pl.ckpt_nc * ns * (pl.qoff ? 1 : 2) * pl.ckpt_stride);
   pl.off_zk = pl.off_npre +
               (pl.post_norm ? align_up((size_t)U * pl.NC * pl.nrows * sizeof(float)) : 0);
   pl.off_rk = pl.off_zk + align_up(tokd);
@@ -252,7 +304,9 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool chain_only = false
   pl.off_rq = pl.off_zq + align_up(tokd);
   pl.as_stride = chain_saved_act_bytes(pl.cfg);
   pl.off_as = pl.off_rq + align_up(tok);
-  pl.ws_bytes_save = pl.off_as + align_up((size_t)U * pl.NC * pl.tpc * ns * pl.as_stride);
+  if (pl.qoff) pl.as_stride = 0;
+  pl.off_wops = pl.off_as + align_up((size_t)U * pl.NC * pl.tpc * ns * pl.as_stride);
+  pl.ws_bytes_save = pl.off_wops + (pl.qoff ? align_up((size_t)pl.ckpt_nc * pl.wslot) : 0);
   pl.off_kwb = 0;
   pl.off_kmb = align_up(ns * tok);
   pl.off_carryb = pl.off_kmb + align_up(ns * tok);
@@ -270,8 +324,12 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool chain_only = false
       pl.off_apart + (pl.affine ? align_up((size_t)U * nb * 2 * d.d * sizeof(float)) : 0);
   // one copy per rank (each accumulates its own rows)
   pl.off_bnx = pl.off_rbar + (pl.post_norm ? align_up((size_t)U * ns * pl.nrows * sizeof(float)) : 0);
-  pl.scratch_bytes =
+  pl.off_qaop =
       pl.off_bnx + (pl.post_norm ? align_up(ngroups * ns * 2 * d.d * sizeof(float)) : 0);
+  // query-side operands of every 32-token tile: Yb_Q, Q and A_Q, Hb_Q
+  const size_t nt = (size_t)U * pl.NC * pl.ntile_max, njb = (d.dh + 31) / 32 * 2;
+  pl.off_qbop = pl.off_qaop + (pl.qoff ? align_up(nt * 2 * (d.d / 16) * 1024) : 0);
+  pl.scratch_bytes = pl.off_qbop + (pl.qoff ? align_up(nt * nmat * njb * 1024) : 0);
   return E2TTT_OK;
 }
 
@@ -426,8 +484,9 @@ e2ttt_status run_forward(const e2ttt_desc* desc, bool chain_only, const float* l
       a.rq = at<float>(workspace, pl.off_rq);
     }
     a.U = pl.U; a.P = pl.P;
-    a.copy = pl.copy; a.wslot = pl.wslot; a.mslot = pl.mslot;
+    a.copy = pl.copy; a.wunit = pl.wunit; a.wslot = pl.wslot; a.mslot = pl.mslot;
     a.T = (int)pl.T; a.C = desc->chunk; a.NC = (int)pl.NC; a.dh = desc->dh;
+    a.toff = 2 * pl.copy;
     a.ntile_max = pl.ntile_max;
     a.resln = (desc->flags & E2TTT_FLAG_NO_RESIDUAL_LN) ? 0 : 1;
     a.eps = desc->ln_eps;
@@ -480,7 +539,43 @@ e2ttt_status run_forward(const e2ttt_desc* desc, bool chain_only, const float* l
     a.nxbuf = at<float>(workspace, pl.off_nx);
     a.norm_pre = save_for_backward ? at<float>(workspace, pl.off_npre) : nullptr;
   }
-  return finish(launch_chain_fwd(pl.cfg, a, s), s, sync);
+  if (!pl.qoff) return finish(launch_chain_fwd(pl.cfg, a, s), s, sync);
+  // the chain over a run of chunks, then their query sides at once
+  a.asave = nullptr;
+  a.copy = save_for_backward ? pl.copy : pl.copy0;
+  a.wunit = save_for_backward ? pl.wunit : pl.wunit0;
+  a.toff = save_for_backward ? 2 * pl.copy : pl.copy0;   // (the T copy's second-layer part)
+  a.wslot = pl.U * a.wunit;
+  a.wops = at<char>(workspace, save_for_backward ? pl.off_wops : pl.off_wops0);
+  TileFwdArgs t{};
+  t.q = q; t.out = out;
+  t.wops = a.wops; t.wslot = a.wslot; t.wunit = a.wunit; t.copy = a.copy;
+  t.toff = a.toff;
+  t.keep = save_for_backward ? 1 : 0;
+  t.zq = a.zq; t.rq = a.rq;
+  t.U = pl.U; t.T = a.T; t.C = a.C; t.NC = a.NC; t.dh = a.dh;
+  t.ntile_max = pl.ntile_max;
+  t.resln = a.resln; t.eps = a.eps;
+  t.ln_a = ln_weight; t.ln_b = ln_bias;
+  t.H = a.H;
+  const int run = save_for_backward ? a.NC : pl.nslot;
+  for (int r = 0; r < a.NC; r += run) {
+    a.r0 = r;
+    a.r1 = std::min(a.NC, r + run);
+    if (r > 0) {
+      a.w_in = w_out;
+      a.m_in = m_out;
+      // the flags anew; line 0, the status, keeps what an earlier launch reported
+      if (sync) e = launch_zero_words(sync + kSyncLine, sync_words(np, pl.cfg.ns) - kSyncLine, s);
+      if (e != hipSuccess) return E2TTT_ERR_HIP;
+    }
+    e = launch_chain_fwd(pl.cfg, a, s);
+    if (e != hipSuccess) return E2TTT_ERR_HIP;
+    t.r = r;
+    e = launch_tile_fwd_query(pl.cfg, t, a.r1 - a.r0, s);
+    if (e != hipSuccess) return E2TTT_ERR_HIP;
+  }
+  return finish(e, s, sync);
 }
 
 }  // namespace e2ttt
@@ -642,9 +737,12 @@ e2ttt_status e2ttt_chunk_backward_ln(const e2ttt_desc* desc, const float* ln_wei
     a.gops = at<char>(scratch, pl.off_gops);
     a.aops = at<char>(scratch, pl.off_baop);
     a.bops = at<char>(scratch, pl.off_bbop);
+    a.qaops = at<char>(scratch, pl.off_qaop);
+    a.qbops = at<char>(scratch, pl.off_qbop);
+    a.qall = pl.qall ? 1 : 0;
     a.ln_zbar = pl.affine ? at<float>(scratch, pl.off_zbar) : nullptr;
     a.U = pl.U; a.P = pl.P;
-    a.copy = pl.copy; a.wslot = pl.wslot; a.mslot = pl.mslot;
+    a.copy = pl.copy; a.wunit = pl.wunit; a.wslot = pl.wslot; a.mslot = pl.mslot;
     a.T = (int)pl.T; a.C = desc->chunk; a.NC = (int)pl.NC; a.dh = desc->dh;
     a.ntile_max = pl.ntile_max;
     a.resln = (desc->flags & E2TTT_FLAG_NO_RESIDUAL_LN) ? 0 : 1;
@@ -708,6 +806,28 @@ e2ttt_status e2ttt_chunk_backward_ln(const e2ttt_desc* desc, const float* ln_wei
     a.norm_pre = const_cast<float*>(at<float>(workspace, pl.off_npre));
     a.norm_rbar = at<float>(scratch, pl.off_rbar);
     a.nxbuf = at<float>(scratch, pl.off_bnx);
+  }
+  if (pl.qoff) {
+    a.asave = nullptr;
+    a.wops = const_cast<char*>(at<char>(workspace, pl.off_wops));
+    a.wslot = pl.wslot;
+    a.wunit = pl.wunit;
+    a.copy = pl.copy;
+    a.qaops = at<char>(scratch, pl.off_qaop);
+    a.qbops = at<char>(scratch, pl.off_qbop);
+    a.nt32 = pl.ntile_max;
+    TileBwdArgs t{};
+    t.q = q; t.d_out = d_out; t.dq = dq;
+    t.wops = a.wops; t.wslot = pl.wslot; t.wunit = pl.wunit; t.copy = pl.copy;
+    t.zq = a.zq; t.rq = a.rq;
+    t.qaops = at<char>(scratch, pl.off_qaop);
+    t.qbops = at<char>(scratch, pl.off_qbop);
+    t.U = pl.U; t.T = a.T; t.C = a.C; t.NC = a.NC; t.dh = a.dh;
+    t.ntile_max = pl.ntile_max;
+    t.resln = a.resln;
+    t.ln_a = ln_weight; t.ln_b = ln_bias;
+    t.H = a.H;
+    if (launch_tile_bwd_query(pl.cfg, t, s) != hipSuccess) return E2TTT_ERR_HIP;
   }
   hipError_t e = launch_chain_bwd(pl.cfg, a, s);
   if (e != hipSuccess) return E2TTT_ERR_HIP;

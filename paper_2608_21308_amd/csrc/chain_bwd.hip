@@ -353,19 +353,21 @@ __device__ __forceinline__ typename S::E* bwd_part(float* slot, int sec) {
 // memory operations were issued before it.  The raw quads take as many
 // registers as the sums with two ranks; with more ranks, load() adds them
 // itself once all are in flight.
-template <class S>
+// DQ: with the dq partials (else dk alone: the query side is elsewhere).
+template <class S, bool DQ>
 struct FlushDkDq {
+  static constexpr int NSEC = DQ ? 2 : 1;
   using Q = typename S::O::Q;
   static constexpr int RPW = row_share<S>();
   static_assert(RPW % 4 == 0, "row shares in whole row quads");
   static constexpr int NV = (RPW / 4) * S::D;
   static constexpr int NPT = (NV + S::NT - 1) / S::NT;   // items per thread
   static constexpr bool RAW = S::NS <= 2;                // sums formed in store()
-  Q raw[RAW ? NPT : 1][2][RAW ? S::NS : 1];
-  f32x4 x[RAW ? 1 : NPT][2];
+  Q raw[RAW ? NPT : 1][NSEC][RAW ? S::NS : 1];
+  f32x4 x[RAW ? 1 : NPT][NSEC];
 
   __device__ __forceinline__ void load(long p, int parity, int tid) {
-    Q q[NPT][2][S::NS];
+    Q q[NPT][NSEC][S::NS];
 #pragma unroll
     for (int a = 0; a < NPT; ++a) {
       // the item's quad; items past the rank's share or the tile (the last
@@ -373,7 +375,7 @@ struct FlushDkDq {
       const int qi = q0 + tid + a * S::NT;
       const int qs = (tid + a * S::NT < NV && qi < (S::CM / 4) * S::D) ? qi : 0;
 #pragma unroll
-      for (int sec = 1; sec <= 2; ++sec)
+      for (int sec = 1; sec <= NSEC; ++sec)
 #pragma unroll
         for (int rk = 0; rk < S::NS; ++rk)
           q[a][sec - 1][rk] = ld_xchg(E2TTT_ARG(xbuf),
@@ -384,7 +386,7 @@ struct FlushDkDq {
 #pragma unroll
       for (int a = 0; a < NPT; ++a)
 #pragma unroll
-        for (int sec = 0; sec < 2; ++sec)
+        for (int sec = 0; sec < NSEC; ++sec)
 #pragma unroll
           for (int rk = 0; rk < S::NS; ++rk) raw[a][sec][rk] = q[a][sec][rk];
     } else {
@@ -392,7 +394,7 @@ struct FlushDkDq {
 #pragma unroll
       for (int a = 0; a < NPT; ++a)
 #pragma unroll
-        for (int sec = 0; sec < 2; ++sec) x[a][sec] = sum_quads(q[a][sec]);
+        for (int sec = 0; sec < NSEC; ++sec) x[a][sec] = sum_quads(q[a][sec]);
     }
   }
   __device__ __forceinline__ void store(long row0, int len, int rlo, int tid) const {
@@ -406,7 +408,7 @@ struct FlushDkDq {
       const int tq = rlo / 4 + v / S::D, i = v % S::D;
       if (v >= NV || 4 * tq >= tend) continue;
 #pragma unroll
-      for (int sec = 1; sec <= 2; ++sec) {
+      for (int sec = 1; sec <= NSEC; ++sec) {
         typename IO::T* d = (sec == 1) ? dk : dq;
         f32x4 xs;
         if constexpr (RAW) xs = sum_quads(raw[a][sec - 1]);
@@ -426,10 +428,10 @@ struct FlushDkDq {
   }
   int q0 = 0;   // quad index of the rank's first row quad, set with the loads
 };
-template <class S>
+template <class S, bool DQ>
 __device__ __forceinline__ void flush_dkdq(long p, int parity, long row0, int len, int rlo,
                                            int tid) {
-  FlushDkDq<S> f;
+  FlushDkDq<S, DQ> f;
   f.q0 = (rlo / 4) * S::D;
   f.load(p, parity, tid);
   f.store(row0, len, rlo, tid);
@@ -443,7 +445,14 @@ __device__ __forceinline__ void flush_dkdq(long p, int parity, long row0, int le
 // transition Wb_0 = cw Wb_C (+ contributions), Mb_0 = cm Wb_C + cb Mb_C right
 // after its P4 as a one-tile chunk does, and every tile adds its contributions
 // to Wb; the chunk's other tiles take their P4 operands from the buffer.
-template <class S, bool LONG, bool PN>
+//
+// QOFF: the query side (its LayerNorm backward, Hb_Q and dq) is done for all
+// chunks at once by a kernel before this one (tile_bwd.hip), since none of it
+// depends on the adjoint state; this kernel only adds its operands' products
+// to Wb.  The forward of such a call has left W_0 in the operand copies.  At 8
+// units and 32 chunks of 64: MLP 128 544 -> 486 us + 11 for the query sides,
+// SwiGLU 172 795 -> 660 + 15.
+template <class S, bool LONG, bool PN, bool QOFF>
 __global__ void __launch_bounds__(S::NT, 1) chain_bwd_kernel(ChainArgs a) {
   using O = typename S::O;
   using E = typename S::E;
@@ -506,6 +515,13 @@ __global__ void __launch_bounds__(S::NT, 1) chain_bwd_kernel(ChainArgs a) {
   // branch, the Q side of this chunk during P7
   TileRegs<S> pK, pV, pQ, pD;
   F32TileRegs<S> pZ, pZq;
+  // QOFF: the query side's A operands of this tile (two 32-token tiles of Yb_Q
+  // and Q, 16 bytes per lane and fragment)
+  constexpr int QV = 2 * 2 * NIB * 64;                    // 16-byte vectors
+  constexpr int QPER = QOFF ? QV / S::NT : 1;
+  static_assert(!QOFF || (QV % S::NT == 0 && QV * 16 <= S::CM * D * 4),
+                "whole vectors per thread, in Y's buffer");
+  u32x4 pqa[QPER];
   float pkw = 0.0f, pkm = 0.0f, prk = 0.0f, prq = 0.0f, pcar = 0.0f;
   auto prefetch_k = [&](long uu, int rc, int kt) {
     E2TTT_LANE_IDS;
@@ -522,8 +538,58 @@ __global__ void __launch_bounds__(S::NT, 1) chain_bwd_kernel(ChainArgs a) {
     }
     if (tid < 3) pcar = E2TTT_ARG(carry)[(uu * NC + rc) * 3 + tid];
   };
+  // W_0 of matrix m at chunk r's start (operand quads): a checkpoint block, or
+  // (QOFF) the R copy of slot r
+  auto load_w0 = [&](Q (&q)[NJB][NIB], const char* blk, int r, long u, int m) {
+    E2TTT_LANE_IDS;
+    if constexpr (QOFF) {
+      const int njb = (dh + 31) / 32 * 2;
+      const bf16x8* src = reinterpret_cast<const bf16x8*>(E2TTT_ARG(wops) + r * E2TTT_ARG(wslot) +
+                                                          u * E2TTT_ARG(wunit));
+#pragma unroll
+      for (int jj = 0; jj < NJB; ++jj) {
+        const int jb = j0 / 16 + w * NJB + jj;
+#pragma unroll
+        for (int p = 0; p < NIB / 2; ++p) {
+          // (blocks past the copies' columns: block 0 loaded, zeroed by zero_w0)
+          const bf16x8 f = ld_stream(src + ((m * njb + (jb < njb ? jb : 0)) * (NIB / 2) + p) * 64 + lane);
+          q[jj][2 * p] = __builtin_shufflevector(f, f, 0, 1, 2, 3);
+          q[jj][2 * p + 1] = __builtin_shufflevector(f, f, 4, 5, 6, 7);
+        }
+      }
+    } else {
+      load_ckpt_mat<S>(q, blk, m, w, lane);
+    }
+  };
+  // ...and, where the loads have had a phase to return, its columns past the copies'
+  auto zero_w0 = [&](Q (&q)[NJB][NIB]) {
+    if constexpr (QOFF) {
+      typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+#pragma unroll
+      for (int jj = 0; jj < NJB; ++jj) {
+        const unsigned keep = j0 / 16 + w * NJB + jj < (dh + 31) / 32 * 2 ? 0xffffffffu : 0u;
+#pragma unroll
+        for (int ib = 0; ib < NIB; ++ib)
+          q[jj][ib] = __builtin_bit_cast(Q, __builtin_bit_cast(u32x2, q[jj][ib]) & keep);
+      }
+    }
+  };
+  // 32-token tiles of chain tile kt of chunk r: its first one's index, and their number
+  auto tile32 = [&](long uu, int r, int kt) { return (uu * NC + r) * E2TTT_ARG(nt32) + kt * (S::CM / 32); };
   auto prefetch_q = [&](long uu, int rc, int kt) {
     E2TTT_LANE_IDS;
+    if constexpr (QOFF) {
+      const int st = LONG ? rc * C + kt * TL : rc * C;
+      const int ln = LONG ? min(TL, min(T, (rc + 1) * C) - st) : min(C, T - st);
+      const u32x4* src = reinterpret_cast<const u32x4*>(E2TTT_ARG(qaops)) +
+                         tile32(uu, rc, kt) * (2 * NIB * 64);
+#pragma unroll
+      for (int v = 0; v < QPER; ++v) {
+        const int e = tid + v * S::NT;
+        pqa[v] = ld_stream(src + (e / (2 * NIB * 64) * 32 < ln ? e : 0));   // (zeroed in P9)
+      }
+      return;
+    }
     const int st = LONG ? rc * C + kt * TL : rc * C;
     const long r0 = uu * T + st;
     const int ln = LONG ? min(TL, min(T, (rc + 1) * C) - st) : min(C, T - st);
@@ -574,14 +640,16 @@ __global__ void __launch_bounds__(S::NT, 1) chain_bwd_kernel(ChainArgs a) {
         const float* npre = E2TTT_ARG(norm_pre) + (u * NC + rc) * R;
         float* rbar = E2TTT_ARG(norm_rbar) + (u * S::NS + rank) * R;
         const bool init = rc == NC - 1;
-        const char* ckN = static_cast<const char*>(E2TTT_ARG(ckpt)) +
-                          ((u * E2TTT_ARG(ckpt_nc) + rc + 1) * S::NS + rank) * 2 *
-                              E2TTT_ARG(ckpt_stride);
+        const char* ckN = QOFF ? nullptr
+                               : static_cast<const char*>(E2TTT_ARG(ckpt)) +
+                                     ((u * E2TTT_ARG(ckpt_nc) + rc + 1) * S::NS + rank) * 2 *
+                                         E2TTT_ARG(ckpt_stride);
         // first-layer rows: hidden unit j is the tile column of lanes c + 16 g
 #pragma unroll
         for (int m = 0; m < NF; ++m) {
           Q wn[NJB][NIB];
-          load_ckpt_mat<S>(wn, ckN, m, w, lane);
+          load_w0(wn, ckN, rc + 1, u, m);
+          zero_w0(wn);
 #pragma unroll
           for (int jj = 0; jj < NJB; ++jj) {
             float A = 0.0f;
@@ -614,7 +682,8 @@ __global__ void __launch_bounds__(S::NT, 1) chain_bwd_kernel(ChainArgs a) {
         static_assert(S::CM >= NW + 2, "LDS room for the row sums");
         float* part = yk;   // [NW][D] wave partials, then [2][D] row factors
         Q wn[NJB][NIB];
-        load_ckpt_mat<S>(wn, ckN, SEC, w, lane);
+        load_w0(wn, ckN, rc + 1, u, SEC);
+        zero_w0(wn);
 #pragma unroll
         for (int ib = 0; ib < NIB; ++ib) {
           float A[4] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -671,8 +740,9 @@ __global__ void __launch_bounds__(S::NT, 1) chain_bwd_kernel(ChainArgs a) {
       // the exchange sequence of this tile starts after the normalisation's
       const unsigned seq0 = px.seq_now();
       const char* ckW = static_cast<const char*>(E2TTT_ARG(ckpt)) +
-                        ((u * E2TTT_ARG(ckpt_nc) + rc) * S::NS + rank) * 2 * E2TTT_ARG(ckpt_stride);
-      const char* ckM = ckW + E2TTT_ARG(ckpt_stride);
+                        ((u * E2TTT_ARG(ckpt_nc) + rc) * S::NS + rank) * (QOFF ? 1 : 2) *
+                            E2TTT_ARG(ckpt_stride);
+      const char* ckM = QOFF ? ckW : ckW + E2TTT_ARG(ckpt_stride);
 
       // chunk-start weights W_0 (kept for the whole chunk), issued first so
       // that P0 and P3 hide them; momentum M_0 (for the carry adjoints after
@@ -682,7 +752,7 @@ __global__ void __launch_bounds__(S::NT, 1) chain_bwd_kernel(ChainArgs a) {
       {
         E2TTT_LANE_IDS;
 #pragma unroll
-        for (int m = 0; m < NMAT; ++m) load_ckpt_mat<S>(w0q[m], ckW, m, w, lane);
+        for (int m = 0; m < NMAT; ++m) load_w0(w0q[m], ckW, rc, u, m);
       }
 
       // ---------------------------------------------------------- P0: stage
@@ -702,6 +772,8 @@ __global__ void __launch_bounds__(S::NT, 1) chain_bwd_kernel(ChainArgs a) {
       __syncthreads();
       {
         E2TTT_LANE_IDS;
+#pragma unroll
+        for (int m = 0; m < NMAT; ++m) zero_w0(w0q[m]);
 #pragma unroll
         for (int m = 0; m < NMAT; ++m) load_ckpt_mat<S>(m0q[m], ckM, m, w, lane);
       }
@@ -1043,7 +1115,7 @@ __global__ void __launch_bounds__(S::NT, 1) chain_bwd_kernel(ChainArgs a) {
       }
       __syncthreads();
       constexpr int P7IT = (S::CM + 4 * NW - 1) / (4 * NW);
-      FlushDkDq<S> flush;
+      FlushDkDq<S, !QOFF> flush;
       float pdyh[S::NS > 1 && PEER_EARLY ? P7IT : 1][S::NS > 1 ? NPEER : 1][EPL];
       if constexpr (S::NS > 1) {
         E2TTT_LANE_IDS;
@@ -1187,7 +1259,9 @@ __global__ void __launch_bounds__(S::NT, 1) chain_bwd_kernel(ChainArgs a) {
       // W_0, GELU' packed), in flight during P8
       Q Aqq[NTB][NJB];
       typename DerivQ<S::BF>::T D1p[SW ? 1 : NTB][SW ? 1 : NJB];
-      if constexpr (!SW) {
+      // QOFF: the query side's B operands, [32-token tile][A_Q, Hb_Q..]
+      bf16x8 qb[QOFF ? 2 : 1][QOFF ? NMAT : 1][NJB];
+      if constexpr (!QOFF && !SW) {
         E2TTT_LANE_IDS;
         const SavedAct<S> sv(static_cast<char*>(E2TTT_ARG(asave)) +
                              (((u * NC + rc) * TPC + kc) * S::NS + rank) * E2TTT_ARG(as_stride));
@@ -1267,6 +1341,24 @@ __global__ void __launch_bounds__(S::NT, 1) chain_bwd_kernel(ChainArgs a) {
             }
             sched_fence();
           }
+        if constexpr (QOFF) {   // in flight during the dk round
+          E2TTT_LANE_IDS;
+          const int njb = (dh + 31) / 32 * 2;
+          const bf16x8* src = reinterpret_cast<const bf16x8*>(E2TTT_ARG(qbops)) +
+                              tile32(u, rc, kc) * (NMAT * njb * 64);
+#pragma unroll
+          for (int t2 = 0; t2 < 2; ++t2)
+#pragma unroll
+            for (int x = 0; x < NMAT; ++x)
+#pragma unroll
+              for (int jj = 0; jj < NJB; ++jj) {
+                const int jb = j0 / 16 + w * NJB + jj;
+                // (no branches around these loads: with them the two-workgroup MLP
+                // spilled 30 VGPRs; those of no block take block 0, zeroed in P9)
+                qb[t2][x][jj] = ld_stream(
+                    src + (t2 * 32 < len && jb < njb ? ((t2 * NMAT + x) * njb + jb) * 64 : 0) + lane);
+              }
+        }
         // dk += Hh W1 (over the hidden index)
 #pragma unroll
         for (int m = 0; m < NF; ++m) {
@@ -1286,7 +1378,43 @@ __global__ void __launch_bounds__(S::NT, 1) chain_bwd_kernel(ChainArgs a) {
       __syncthreads();
 
       // -------------------------------------------- P9: output branch
-      {
+      if constexpr (QOFF) {
+        E2TTT_LANE_IDS;
+        // its operands: Wb2 += Yb_Q^T A_Q, Wb1 += Q^T Hb_Q per 32-token tile
+        u32x4* const qa = reinterpret_cast<u32x4*>(yk);   // (Z is not needed any more)
+#pragma unroll
+        for (int v = 0; v < QPER; ++v) {
+          const int e = tid + v * S::NT;
+          qa[e] = pqa[v] & (e / (2 * NIB * 64) * 32 < len ? 0xffffffffu : 0u);
+        }
+        __syncthreads();
+        if (r >= 0) prefetch_k(u, r, kt);              // the next tile (r, kt advanced above)
+        opaque_state<S>(Wb);
+        const int njb = (dh + 31) / 32 * 2;
+        const bf16x8* const fa = reinterpret_cast<const bf16x8*>(qa) + lane;
+#pragma unroll
+        for (int t2 = 0; t2 < 2; ++t2) {
+#pragma unroll
+          for (int jj = 0; jj < NJB; ++jj) {
+            const unsigned keep = t2 * 32 < len && j0 / 16 + w * NJB + jj < njb ? 0xffffffffu : 0u;
+            bf16x8 ob[NMAT];
+#pragma unroll
+            for (int x = 0; x < NMAT; ++x)
+              ob[x] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, qb[t2][x][jj]) & keep);
+#pragma unroll
+            for (int ib = 0; ib < NIB; ++ib) {
+              const bf16x8 fy = fa[(t2 * 2 * NIB + ib) * 64], fq = fa[((t2 * 2 + 1) * NIB + ib) * 64];
+              Wb.t[SEC][jj][ib] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fy, ob[0],
+                                                                          Wb.t[SEC][jj][ib], 0, 0, 0);
+#pragma unroll
+              for (int m = 0; m < NF; ++m)
+                Wb.t[m][jj][ib] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fq, ob[1 + m],
+                                                                          Wb.t[m][jj][ib], 0, 0, 0);
+              sched_fence();
+            }
+          }
+        }
+      } else {
         E2TTT_LANE_IDS;
         E* xq = xk;                                      // Q [t][i]
         E* xdo = reinterpret_cast<E*>(rr);               // dO [t][i]
@@ -1487,7 +1615,7 @@ __global__ void __launch_bounds__(S::NT, 1) chain_bwd_kernel(ChainArgs a) {
       px.post();                                    // the last tile's dk, dq partials
       px.wait_for(px.seq_now(), sword);             // the peers'
       if (pend_s0 >= 0)
-        flush_dkdq<S>(px.xs, pend_par, u * T + pend_s0, pend_len, rlo, tid);
+        flush_dkdq<S, !QOFF>(px.xs, pend_par, u * T + pend_s0, pend_len, rlo, tid);
       __syncthreads();
     }
     // w_in also sets the targets t_r = |w_in,r|: d_w_in,r += (sum over the
@@ -1536,31 +1664,38 @@ __global__ void __launch_bounds__(S::NT, 1) chain_bwd_kernel(ChainArgs a) {
   }
 }
 
-template <class S, bool LONG, bool PN>
+template <class S, bool LONG, bool PN, bool QOFF>
 int occupancy() {
   int v = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, chain_bwd_kernel<S, LONG, PN>, S::NT, 0) !=
-      hipSuccess)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, chain_bwd_kernel<S, LONG, PN, QOFF>, S::NT,
+                                                   0) != hipSuccess)
     v = 0;
   return v;
 }
 
+// the shapes with a kernel that leaves the query side out
+template <class S>
+constexpr bool kQoff = S::BF && S::D == 64;
+
 template <class S>
 int max_blocks_per_cu() {
   static int nb = [] {
-    // one launch geometry serves both chunk-length instantiations
+    // one launch geometry serves every instantiation
     constexpr bool PN = E2TTT_CHAIN_PN;
-    return std::min(occupancy<S, false, PN>(), occupancy<S, true, PN>());
+    int v = std::min(occupancy<S, false, PN, false>(), occupancy<S, true, PN, false>());
+    if constexpr (kQoff<S>)
+      v = std::min(v, std::min(occupancy<S, false, PN, true>(), occupancy<S, true, PN, true>()));
+    return v;
   }();
   return nb;
 }
 
-template <class S, bool LONG, bool PN>
+template <class S, bool LONG, bool PN, bool QOFF>
 hipError_t launch_as(const ChainArgs& a, hipStream_t stream) {
   // (several workgroups per unit: why a plain launch will do is in pair_xchg.h)
   const long blocks = S::NS == 1 ? a.U : S::NS * a.npairs;
-  hipLaunchKernelGGL((chain_bwd_kernel<S, LONG, PN>), dim3((unsigned)blocks), dim3(S::NT), 0, stream,
-                     a);
+  hipLaunchKernelGGL((chain_bwd_kernel<S, LONG, PN, QOFF>), dim3((unsigned)blocks), dim3(S::NT), 0,
+                     stream, a);
   return hipGetLastError();
 }
 
@@ -1570,9 +1705,14 @@ hipError_t launch(const ChainArgs& a, hipStream_t stream) {
   // kernels without it carry none of its registers
   constexpr bool PN = E2TTT_CHAIN_PN;
   if ((a.norm_tgt != nullptr) != PN) return hipErrorInvalidValue;
-  if (a.C <= S::CM) return launch_as<S, false, PN>(a, stream);
-  if (!a.bfrz) return hipErrorInvalidValue;
-  return launch_as<S, true, PN>(a, stream);
+  const bool lng = a.C > S::CM;
+  if (lng && !a.bfrz) return hipErrorInvalidValue;
+  if (a.wops) {
+    if constexpr (kQoff<S>)
+      return lng ? launch_as<S, true, PN, true>(a, stream) : launch_as<S, false, PN, true>(a, stream);
+    return hipErrorInvalidValue;
+  }
+  return lng ? launch_as<S, true, PN, false>(a, stream) : launch_as<S, false, PN, false>(a, stream);
 }
 
 }  // namespace

@@ -55,22 +55,24 @@ struct FwdSmemBase {
   static constexpr bool Q2 = BYTES + S::CM * S::LDH * (int)sizeof(E) <= 160 * 1024;
 };
 
-template <class S>
+template <class S, bool QOFF>
 struct FwdSmem {
   using E = typename S::E;
-  static constexpr bool Q2 = FwdSmemBase<S>::Q2;
+  static constexpr bool Q2 = !QOFF && FwdSmemBase<S>::Q2;
   alignas(16) E xk[S::CM * S::LDD];
-  alignas(16) E xq[S::CM * S::LDD];
+  alignas(16) E xq[QOFF ? 8 : S::CM * S::LDD];
   alignas(16) E xv[S::CM * S::LDD];
   alignas(16) E kt[S::D * S::LDC];    // K^T, layout [i][t] (it_idx)
   alignas(16) E alds[S::CM * S::LDH]; // activations A[t][j] (this workgroup's columns)
   alignas(16) E alds2[Q2 ? S::CM * S::LDH : 8]; // Q-side activations (else alds)
+  // QOFF, saving: first-layer weights, laid out as w2
+  alignas(16) E w1[QOFF ? (S::NMAT - 1) * S::D * S::LDH : 8];
   alignas(16) E w2[S::D * S::LDH];    // second-layer weights W2[i][j] (bf16/fp32 copy of W_0)
   alignas(16) E dy[S::CM * S::LDD];   // dY[t][i]
   alignas(16) E dytw[S::D * S::LDC];  // K^W_t dY[t][i], layout [i][t] (it_idx)
   alignas(16) E dytm[S::D * S::LDC];  // K^M_t dY[t][i]
   alignas(16) float y[S::CM * S::D];  // Y_K (partial over this workgroup's columns)
-  alignas(16) float yq[S::CM * S::D]; // Y_Q (partial)
+  alignas(16) float yq[QOFF ? 4 : S::CM * S::D]; // Y_Q (partial)
   alignas(16) float kw[S::CM];
   alignas(16) float km[S::CM];
   float carry[4];
@@ -86,7 +88,8 @@ struct FwdSmem {
 // of Y_K where the peers load its rows right after their wait for it (before
 // posting their Y_Q of the same tile, which the rank waits for before the next
 // Y_K); where the row phases read Y_K from the slots later in the tile (after
-// that post), Y_K alternates between two slots.  Fewer slots keep the
+// that post), and without Y_Q swaps (QOFF: the next order between the ranks is
+// the post of the next Y_K), Y_K alternates between two slots.  Fewer slots keep the
 // exchange's working set in the XCD's L2.
 template <class S, int NPK>
 __device__ __forceinline__ float* fwd_slot_k(float* xbuf, long p, int rank, int parity) {
@@ -99,7 +102,16 @@ __device__ __forceinline__ float* fwd_slot_q(float* xbuf, long p, int rank) {
 
 // LONG: chunks longer than the CM-row tile (a separate instantiation, so that
 // the common case keeps W_0's operand copies dead between chunks).
-template <class S, bool LONG, bool PN>
+//
+// QOFF: the query side is left to a kernel over all chunks at once
+// (tile_fwd.hip), which reads the operand copies of every chunk's W_0 that
+// this kernel leaves in memory.  With few units most of the device is idle
+// beside the chain, and a chunk's query side took a quarter of its time; the
+// copies are written while the chunk waits for the peers' Y_K.  Saving, 8 units
+// and 32 chunks of 64: MLP 128 330 -> 244 us + 8 for the query sides, SwiGLU
+// 172 410 -> 326 + 12.  Chunks [r0, r1) per launch, the state in w_out / m_out
+// between launches.
+template <class S, bool LONG, bool PN, bool QOFF>
 __global__ void __launch_bounds__(S::NT, 1) chain_fwd_kernel(ChainArgs a) {
   using O = typename S::O;
   using IO = IoT<S::BF>;
@@ -131,14 +143,16 @@ __global__ void __launch_bounds__(S::NT, 1) chain_fwd_kernel(ChainArgs a) {
   // peers or wide rows that would hold too many registers, and each row
   // phase loads them where it adds them
   constexpr bool PEER_EARLY = NPEER * EPL <= 8 && S::D <= 64;
-  constexpr int NPK = PEER_EARLY ? 1 : 2;   // Y_K slots per rank
-  __shared__ FwdSmem<S> sm;
-  static_assert(sizeof(FwdSmem<S>) <= 160 * 1024, "LDS budget");
+  constexpr int NPK = (PEER_EARLY && !QOFF) ? 1 : 2;   // Y_K slots per rank
+  using Smem = FwdSmem<S, QOFF>;
+  __shared__ Smem sm;
+  static_assert(sizeof(Smem) <= 160 * 1024, "LDS budget");
 
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int T = a.T, C = a.C, NC = a.NC, dh = a.dh;
   const int TPC = LONG ? (C + S::CM - 1) / S::CM : 1;   // tiles per chunk
   const int TL = LONG ? S::CM : C;                       // tokens per tile
+  const int R0 = QOFF ? a.r0 : 0, R1 = QOFF ? a.r1 : NC; // chunks of this launch
   const float inv_d = 1.0f / D;
 
   PairX<S::NS> px;
@@ -153,7 +167,7 @@ __global__ void __launch_bounds__(S::NT, 1) chain_fwd_kernel(ChainArgs a) {
   // hidden columns [DHP, DHK) of the j-operands stay zero for the whole run
   if constexpr (S::DHK > S::DHP) {
     jq_zero_cols<S, S::LDH, S::DHK>(sm.alds, S::NTB, sm.w2, S::NIB, S::DHP);
-    if constexpr (FwdSmem<S>::Q2) jq_zero_cols<S, S::LDH, S::DHK>(sm.alds2, S::NTB, sm.alds2, 0, S::DHP);
+    if constexpr (Smem::Q2) jq_zero_cols<S, S::LDH, S::DHK>(sm.alds2, S::NTB, sm.alds2, 0, S::DHP);
   }
 
   // inputs of the next chunk, loaded one chunk ahead
@@ -165,7 +179,7 @@ __global__ void __launch_bounds__(S::NT, 1) chain_fwd_kernel(ChainArgs a) {
     const long r0 = uu * T + st;
     const int ln = LONG ? min(TL, min(T, (rc + 1) * C) - st) : min(C, T - st);
     pk.load(E2TTT_ARG(k), r0, ln, tid);
-    pq.load(E2TTT_ARG(q), r0, ln, tid);
+    if constexpr (!QOFF) pq.load(E2TTT_ARG(q), r0, ln, tid);
     pv.load(E2TTT_ARG(v), r0, ln, tid);
     if (tid < S::CM) {
       pkw = (tid < ln) ? E2TTT_ARG(kw)[r0 + tid] : 0.0f;
@@ -183,10 +197,10 @@ __global__ void __launch_bounds__(S::NT, 1) chain_fwd_kernel(ChainArgs a) {
       load_state<S>(W, E2TTT_ARG(w_in) + u * a.P, dh, j0, w, g, c);
       load_state<S>(M, E2TTT_ARG(m_in) ? E2TTT_ARG(m_in) + u * a.P : nullptr, dh, j0, w, g, c);
     }
-    prefetch(u, 0, 0);
+    prefetch(u, R0, 0);
 
     // tile kt of chunk r (always kt = 0 unless LONG)
-    for (int r = 0, kt = 0; r < NC; ++nch) {
+    for (int r = R0, kt = 0; r < R1; ++nch) {
       const int s0 = LONG ? r * C + kt * TL : r * C;
       const int cend = LONG ? min(T, (r + 1) * C) : 0;
       const bool first = !LONG || kt == 0;         // the chunk's first tile
@@ -201,7 +215,7 @@ __global__ void __launch_bounds__(S::NT, 1) chain_fwd_kernel(ChainArgs a) {
       {
       E2TTT_LANE_IDS;
       pk.store(sm.xk, tid);
-      pq.store(sm.xq, tid);
+      if constexpr (!QOFF) pq.store(sm.xq, tid);
       pv.store(sm.xv, tid);
       if (tid < S::CM) {
         sm.kw[tid] = pkw;
@@ -232,7 +246,7 @@ __global__ void __launch_bounds__(S::NT, 1) chain_fwd_kernel(ChainArgs a) {
               XM.t[m][jj][ib] = zero4();
             }
       }
-      if (E2TTT_ARG(ckpt)) {
+      if (!QOFF && E2TTT_ARG(ckpt)) {
         char* cb = static_cast<char*>(E2TTT_ARG(ckpt)) +
                    ((u * E2TTT_ARG(ckpt_nc) + rc) * S::NS + rank) * 2 * E2TTT_ARG(ckpt_stride);
         if constexpr (PRESPLIT) store_ckpt_q<S>(WS.hi, cb, w, lane);
@@ -246,12 +260,24 @@ __global__ void __launch_bounds__(S::NT, 1) chain_fwd_kernel(ChainArgs a) {
         for (int ib = 0; ib < NIB; ++ib)
           jq_put<S, S::LDH>(sm.w2, ib, g, 16 * (w * NJB + jj) + c,
                             as_quad<S>(PRESPLIT ? WS.hi[SEC][jj][ib] : O::cvt(W.t[SEC][jj][ib])));
+      if constexpr (QOFF) {
+        if (E2TTT_ARG(ckpt)) {
+#pragma unroll
+          for (int m = 0; m < SEC; ++m)
+#pragma unroll
+            for (int jj = 0; jj < NJB; ++jj)
+#pragma unroll
+              for (int ib = 0; ib < NIB; ++ib)
+                jq_put<S, S::LDH>(sm.w1 + m * D * S::LDH, ib, g, 16 * (w * NJB + jj) + c,
+                                  as_quad<S>(PRESPLIT ? WS.hi[m][jj][ib] : O::cvt(W.t[m][jj][ib])));
+        }
+      }
       }
       opaque_state<S>(W);
       opaque_state<S>(M);
       }
       __syncthreads();
-      if (r < NC) prefetch(u, r, kt);              // the next tile (r, kt advanced above)
+      if (r < R1) prefetch(u, r, kt);              // the next tile (r, kt advanced above)
 
       // operand of the chunk's products (W_0: W is not updated before the chunk end
       // on the fp32 path, nor before the transition below on the others)
@@ -321,16 +347,79 @@ __global__ void __launch_bounds__(S::NT, 1) chain_fwd_kernel(ChainArgs a) {
                         (S::NS > 1) ? fwd_slot_k<S, NPK>(E2TTT_ARG(xbuf), px.xs, rank, par) : nullptr);
       }
       px.post();                                          // seq0 + 1: Y_K
+      if constexpr (QOFF) {
+        // the operand copies of this chunk's W_0 for the query side (tile_common.h's
+        // R and T layouts), and the checkpoint of M_0 for the backward: issued here,
+        // where the chunk waits for the peers' Y_K
+        if (first) {
+          E2TTT_LANE_IDS;
+          const int dhb = (dh + 31) / 32, njb = 2 * dhb;
+          const bool save = E2TTT_ARG(ckpt) != nullptr;
+          const long cpy = E2TTT_ARG(copy);
+          char* const rh = E2TTT_ARG(wops) + (rc - (save ? 0 : R0)) * E2TTT_ARG(wslot) + u * E2TTT_ARG(wunit);
+          bf16x8* const vr = reinterpret_cast<bf16x8*>(rh);
+          bf16x8* const vl = reinterpret_cast<bf16x8*>(rh + cpy);
+          bf16x8* const vt = reinterpret_cast<bf16x8*>(rh + E2TTT_ARG(toff));
+          auto join = [](const bf16x4& x, const bf16x4& y) {
+            return __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7);
+          };
+#pragma unroll
+          for (int jj = 0; jj < NJB; ++jj) {
+            const int jb = j0 / 16 + w * NJB + jj;
+            if (jb < njb) {
+#pragma unroll
+              for (int m = 0; m < NMAT; ++m) {
+                if (m == SEC && !save) continue;   // (the query side takes W2's T copy)
+#pragma unroll
+                for (int p = 0; p < NIB / 2; ++p) {
+                  typename O::Q hi[2], lo[2];
+#pragma unroll
+                  for (int h = 0; h < 2; ++h) {
+                    if constexpr (PRESPLIT) {
+                      hi[h] = WS.hi[m][jj][2 * p + h];
+                      lo[h] = WS.lo[m][jj][2 * p + h];
+                    } else {
+                      const f32x4 v = W.t[m][jj][2 * p + h];
+                      hi[h] = O::cvt(v);
+                      lo[h] = O::cvt(v - quad_f32(hi[h]));
+                    }
+                  }
+                  const int fr = ((m * njb + jb) * (NIB / 2) + p) * 64 + lane;
+                  st_stream(vr + fr, join(hi[0], hi[1]));
+                  if (m < SEC) st_stream(vl + fr, join(lo[0], lo[1]));
+                }
+              }
+            }
+          }
+          // T copies: the [i][j] LDS operands read as fragments
+          constexpr int NQ = S::DHP / 32;
+          for (int x = w; x < NIB * NQ; x += S::NW) {
+            const int ib = x / NQ, q = j0 / 32 + x % NQ;
+            if (q >= dhb) continue;
+#pragma unroll
+            for (int m = 0; m < NMAT; ++m) {
+              if (m < SEC && !save) continue;
+              const typename S::E* src = m < SEC ? sm.w1 + m * D * S::LDH : sm.w2;
+              const auto f = jq_frag<S>(jq_lane<S, S::LDH>(src, ib, g, c), (x % NQ) * 32);
+              st_stream(vt + ((m * NIB + ib) * dhb + q) * 64 + lane, join(f.h[0], f.h[1]));
+            }
+          }
+          if (save)
+            store_ckpt<S>(M, static_cast<char*>(E2TTT_ARG(ckpt)) +
+                                 ((u * E2TTT_ARG(ckpt_nc) + rc) * S::NS + rank) * E2TTT_ARG(ckpt_stride),
+                          w, lane);
+        }
+      }
       // without a separate Q-side buffer, alds is rewritten below
-      if constexpr (!FwdSmem<S>::Q2 && S::NS == 1) __syncthreads();
-      typename S::E* const aq = FwdSmem<S>::Q2 ? sm.alds2 : sm.alds;
+      if constexpr (!QOFF && !Smem::Q2 && S::NS == 1) __syncthreads();
+      typename S::E* const aq = Smem::Q2 ? sm.alds2 : sm.alds;
 
       // ------------------- Q-side first layer and Y_Q (a7), overlapping the swap
       // (MLP, saving for the backward: A_Q and GELU'(H_Q) of every tile)
       typename O::Q qsa[S::FW == 0 ? NTB : 1][NJB];
       f32x4 qsd[S::FW == 0 ? NTB : 1][NJB];
-      if constexpr (RELOAD) w0_mats(0, 1);
-      {
+      if constexpr (RELOAD && !QOFF) w0_mats(0, 1);
+      if constexpr (!QOFF) {
       E2TTT_LANE_IDS;
       opaque_state<S>(W);
 #pragma unroll
@@ -391,6 +480,7 @@ __global__ void __launch_bounds__(S::NT, 1) chain_fwd_kernel(ChainArgs a) {
       } else {
         __syncthreads();
       }
+      if constexpr (!QOFF) {
       {
         E2TTT_LANE_IDS;
         jgemm_to_lds<S>(aq, sm.w2, sm.yq, w, g, c,        // Y_Q (partial)
@@ -411,6 +501,7 @@ __global__ void __launch_bounds__(S::NT, 1) chain_fwd_kernel(ChainArgs a) {
             st_stream(sv.aq() + qi, qsa[tb][jj]);
             st_stream(sv.d1q() + qi, DerivQ<S::BF>::pack(qsd[tb][jj]));
           }
+      }
       }
 
       // ------------------------------- LN and activation gradients (a4)
@@ -533,7 +624,7 @@ __global__ void __launch_bounds__(S::NT, 1) chain_fwd_kernel(ChainArgs a) {
       // that they arrive under dA and the state update.
       constexpr int NITO = (RPW + 4 * S::NW - 1) / (4 * S::NW);
       float pyq[S::NS > 1 && PEER_EARLY ? NITO : 1][S::NS > 1 ? NPEER : 1][EPL];
-      if constexpr (S::NS > 1) {
+      if constexpr (S::NS > 1 && !QOFF) {
         px.wait_for(seq0 + 2, sm.word);                   // peers' Y_Q
         E2TTT_LANE_IDS;
 #pragma unroll
@@ -734,7 +825,7 @@ __global__ void __launch_bounds__(S::NT, 1) chain_fwd_kernel(ChainArgs a) {
       }
 
       // ------------------------------------------------- outputs (a7)
-      {
+      if constexpr (!QOFF) {
         E2TTT_LANE_IDS;
         using IOT = typename IO::T;
         IOT* outp = reinterpret_cast<IOT*>(E2TTT_ARG(out)) + row0 * D;
@@ -810,7 +901,28 @@ __global__ void __launch_bounds__(S::NT, 1) chain_fwd_kernel(ChainArgs a) {
       E2TTT_LANE_IDS;
       // with the normalisation the backward also needs the final (normalised)
       // weights: one more checkpoint block, W only
-      if (PN && E2TTT_ARG(ckpt))
+      if constexpr (PN && QOFF) {
+        if (E2TTT_ARG(ckpt) && R1 == NC) {
+          const int njb = (dh + 31) / 32 * 2;
+          bf16x8* const vr = reinterpret_cast<bf16x8*>(E2TTT_ARG(wops) + NC * E2TTT_ARG(wslot) +
+                                                       u * E2TTT_ARG(wunit));
+#pragma unroll
+          for (int jj = 0; jj < NJB; ++jj) {
+            const int jb = j0 / 16 + w * NJB + jj;
+            if (jb < njb) {
+#pragma unroll
+              for (int m = 0; m < NMAT; ++m)
+#pragma unroll
+                for (int p = 0; p < NIB / 2; ++p)
+                  st_stream(vr + ((m * njb + jb) * (NIB / 2) + p) * 64 + lane,
+                            __builtin_shufflevector(O::cvt(W.t[m][jj][2 * p]),
+                                                    O::cvt(W.t[m][jj][2 * p + 1]), 0, 1, 2, 3, 4,
+                                                    5, 6, 7));
+            }
+          }
+        }
+      }
+      if (PN && !QOFF && E2TTT_ARG(ckpt))
         store_ckpt<S>(W, static_cast<char*>(E2TTT_ARG(ckpt)) +
                              ((u * E2TTT_ARG(ckpt_nc) + NC) * S::NS + rank) * 2 *
                                  E2TTT_ARG(ckpt_stride), w, lane);
@@ -820,31 +932,38 @@ __global__ void __launch_bounds__(S::NT, 1) chain_fwd_kernel(ChainArgs a) {
   }
 }
 
-template <class S, bool LONG, bool PN>
+template <class S, bool LONG, bool PN, bool QOFF>
 int occupancy() {
   int v = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, chain_fwd_kernel<S, LONG, PN>, S::NT, 0) !=
-      hipSuccess)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, chain_fwd_kernel<S, LONG, PN, QOFF>, S::NT,
+                                                   0) != hipSuccess)
     v = 0;
   return v;
 }
 
+// the shapes with a kernel that leaves the query side out
+template <class S>
+constexpr bool kQoff = S::BF && S::D == 64;
+
 template <class S>
 int max_blocks_per_cu() {
   static int nb = [] {
-    // one launch geometry serves both chunk-length instantiations
+    // one launch geometry serves every instantiation
     constexpr bool PN = E2TTT_CHAIN_PN;
-    return std::min(occupancy<S, false, PN>(), occupancy<S, true, PN>());
+    int v = std::min(occupancy<S, false, PN, false>(), occupancy<S, true, PN, false>());
+    if constexpr (kQoff<S>)
+      v = std::min(v, std::min(occupancy<S, false, PN, true>(), occupancy<S, true, PN, true>()));
+    return v;
   }();
   return nb;
 }
 
-template <class S, bool LONG, bool PN>
+template <class S, bool LONG, bool PN, bool QOFF>
 hipError_t launch_as(const ChainArgs& a, hipStream_t stream) {
   // (several workgroups per unit: why a plain launch will do is in pair_xchg.h)
   const long blocks = S::NS == 1 ? a.U : S::NS * a.npairs;
-  hipLaunchKernelGGL((chain_fwd_kernel<S, LONG, PN>), dim3((unsigned)blocks), dim3(S::NT), 0, stream,
-                     a);
+  hipLaunchKernelGGL((chain_fwd_kernel<S, LONG, PN, QOFF>), dim3((unsigned)blocks), dim3(S::NT), 0,
+                     stream, a);
   return hipGetLastError();
 }
 
@@ -854,10 +973,15 @@ hipError_t launch(const ChainArgs& a, hipStream_t stream) {
   // kernels without it carry none of its registers
   constexpr bool PN = E2TTT_CHAIN_PN;
   if ((a.norm_tgt != nullptr) != PN) return hipErrorInvalidValue;
-  if (a.C <= S::CM) return launch_as<S, false, PN>(a, stream);
+  const bool lng = a.C > S::CM;
   // a long chunk whose products re-form W_0 from the state needs the W_0 blocks
-  if (S::BF && (S::FW == 1 || S::D > 64) && !a.w0blk) return hipErrorInvalidValue;
-  return launch_as<S, true, PN>(a, stream);
+  if (lng && S::BF && (S::FW == 1 || S::D > 64) && !a.w0blk) return hipErrorInvalidValue;
+  if (a.wops) {
+    if constexpr (kQoff<S>)
+      return lng ? launch_as<S, true, PN, true>(a, stream) : launch_as<S, false, PN, true>(a, stream);
+    return hipErrorInvalidValue;
+  }
+  return lng ? launch_as<S, true, PN, false>(a, stream) : launch_as<S, false, PN, false>(a, stream);
 }
 
 }  // namespace

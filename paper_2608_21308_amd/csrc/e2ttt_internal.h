@@ -130,6 +130,19 @@ struct ChainArgs {
   float* norm_rbar;       // [U][NS][R] backward: what flows into the targets, per rank
   float* nxbuf;           // [groups][NS][2][d] second-layer row sums of each rank
   long ckpt_nc;           // checkpoint blocks per unit: NC, or NC + 1 (the final state)
+  // query side left to kernels over all chunks (nullable: in the chain).  The
+  // operand copies of each chunk's W_0 (tile_common.h), [slot][U][R high | R low |
+  // T], slot r when saving, else r - r0; the checkpoints then hold M only.
+  char* wops;
+  long wslot;             // bytes of a slot
+  long wunit;             // bytes between units in it
+  long copy, toff;        // bytes from a unit's R high to its R low, to its T
+  int r0, r1;             // forward: the chunks of this launch
+  // backward: the query side's operands of the state sums, per unit, chunk and
+  // 32-token tile (nt32 per chunk): A operands [Yb_Q, Q], B operands [A_Q, Hb_Q..]
+  const char* qaops;
+  const char* qbops;
+  int nt32;
 };
 // Post-chunk normalisation: the target norms of every unit's rows from w_in.
 hipError_t launch_norm_targets(const float* w_in, float* tgt, long U, int d, int dh, int nmat,

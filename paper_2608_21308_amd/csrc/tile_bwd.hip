@@ -26,14 +26,17 @@ namespace e2ttt {
 namespace {
 
 template <class G>
-struct BwdTileSmem {
-  // Hh of pass 1, one f32x4 per lane, matrix, 16-column block and token block
-  alignas(16) f32x4 hh[G::NF * G::MAXQ * 4 * 256];
+struct BwdQuerySmem {
   alignas(16) float red[2 * G::RED];       // also the K^T buffer of the first row phase
   alignas(16) Bf xt[G::TI];                // K | Q
   alignas(16) Bf ti[G::TI];                // dY, then Yh | Yb_Q
   alignas(16) Bf it[G::IT];                // dY^T, then Yh^T | Yb_Q^T
   alignas(16) Bf tr[4][G::TR];
+};
+template <class G>
+struct BwdTileSmem : BwdQuerySmem<G> {
+  // Hh of pass 1, one f32x4 per lane, matrix, 16-column block and token block
+  alignas(16) f32x4 hh[G::NF * G::MAXQ * 4 * 256];
   float kb[2][4][kTileTok];                // dK^W, dK^M partials of the waves
 };
 
@@ -202,10 +205,10 @@ __device__ void bwd_key_tile(const TileBwdArgs& a, BwdTileSmem<G>& sm, long u, i
   const int lane = tid & 63, g = lane >> 4, c = lane & 15, i0 = c * EPL;
   const int dhb = (a.dh + 31) / 32, njb = 2 * dhb;
   const bf16x8* const w0 =
-      reinterpret_cast<const bf16x8*>(a.wops + a.r * a.wslot + u * 3 * a.copy);
+      reinterpret_cast<const bf16x8*>(a.wops + a.r * a.wslot + u * a.wunit);
   const bf16x8* const gb = reinterpret_cast<const bf16x8*>(a.gops + u * 4 * a.copy);
-  char* const bop = a.bops + (u * a.ntile_max + tile) * (long)G::NB_BWD * njb * 1024;
-  char* const aop = a.aops + (u * a.ntile_max + tile) * (long)G::NA_BWD * G::NIB * 1024;
+  char* const bop = a.bops + (u * a.ntile_max + tile) * (long)G::NB_KEY * njb * 1024;
+  char* const aop = a.aops + (u * a.ntile_max + tile) * (long)G::NA_KEY * G::NIB * 1024;
   const float inv_d = 1.0f / D;
   constexpr int AOP = G::NIB * 1024;
 
@@ -449,17 +452,14 @@ __device__ void bwd_key_tile(const TileBwdArgs& a, BwdTileSmem<G>& sm, long u, i
 }
 
 template <class G>
-__device__ void bwd_query_tile(const TileBwdArgs& a, BwdTileSmem<G>& sm, long u, int tile, int len,
-                               long row0) {
+__device__ void bwd_query_tile(const TileBwdArgs& a, BwdQuerySmem<G>& sm, long u, int chunk,
+                               int len, long row0, char* aop, char* bop) {
   constexpr int D = G::D, EPL = G::EPL, NF = G::NF;
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15, i0 = c * EPL;
   const int dhb = (a.dh + 31) / 32, njb = 2 * dhb;
   const bf16x8* const w0 =
-      reinterpret_cast<const bf16x8*>(a.wops + a.r * a.wslot + u * 3 * a.copy);
-  char* const bop = a.bops + (u * a.ntile_max + tile) * (long)G::NB_BWD * njb * 1024 +
-                    (long)(2 + NF) * njb * 1024;
-  char* const aop = a.aops + (u * a.ntile_max + tile) * (long)G::NA_BWD * G::NIB * 1024;
+      reinterpret_cast<const bf16x8*>(a.wops + chunk * a.wslot + u * a.wunit);
   const float inv_d = 1.0f / D;
   constexpr int AOP = G::NIB * 1024;
   const Bf* qp = static_cast<const Bf*>(a.q) + row0 * D;
@@ -496,8 +496,8 @@ __device__ void bwd_query_tile(const TileBwdArgs& a, BwdTileSmem<G>& sm, long u,
     put_ti<G>(sm.xt, t, i0, x);
   }
   __syncthreads();
-  flush_it<G>(aop + 3 * AOP, sm.it, w, lane, g, c);
-  flush_it<G>(aop + 4 * AOP, qt, w, lane, g, c);
+  flush_it<G>(aop, sm.it, w, lane, g, c);
+  flush_it<G>(aop + AOP, qt, w, lane, g, c);
   f32x4 dq[G::NIB][2];
 #pragma unroll
   for (int ib = 0; ib < G::NIB; ++ib) dq[ib][0] = dq[ib][1] = zero4();
@@ -577,7 +577,7 @@ template <class G>
 __global__ void __launch_bounds__(256, 1) tile_bwd_token_kernel(TileBwdArgs a) {
   __shared__ BwdTileSmem<G> sm;
   static_assert(sizeof(BwdTileSmem<G>) <= 160 * 1024, "LDS budget");
-  const TileBlock b = tile_block(blockIdx.x, a.U, 2 * a.ntile);
+  const TileBlock b = tile_block(blockIdx.x, a.U, a.qall ? a.ntile : 2 * a.ntile);
   if (b.u >= a.U) return;
   const bool key = b.item < a.ntile;     // the key side takes longer and goes first
   const int tile = key ? b.item : b.item - a.ntile;
@@ -585,7 +585,31 @@ __global__ void __launch_bounds__(256, 1) tile_bwd_token_kernel(TileBwdArgs a) {
   const int len = min(kTileTok, min(a.T, (a.r + 1) * a.C) - s0);
   const long row0 = b.u * a.T + s0;
   if (key) bwd_key_tile<G>(a, sm, b.u, tile, len, row0);
-  else bwd_query_tile<G>(a, sm, b.u, tile, len, row0);
+  else {
+    const long t = b.u * a.ntile_max + tile;
+    const int njb = (a.dh + 31) / 32 * 2;
+    bwd_query_tile<G>(a, sm, b.u, a.r, len, row0, a.qaops + t * (G::NA_QRY * G::NIB * 1024),
+                      a.qbops + t * (G::NB_QRY * njb * 1024L));
+  }
+}
+
+// The query side alone, of every chunk at once: none of it depends on the
+// adjoint state.  Ahead of a chain that leaves it out (chain_bwd.hip, QOFF), and
+// of the chunks' token kernels where one chunk's tiles do not fill the device.
+template <class G>
+__global__ void __launch_bounds__(256, 1) tile_bwd_query_kernel(TileBwdArgs a) {
+  __shared__ BwdQuerySmem<G> sm;
+  const TileBlock b = tile_block(blockIdx.x, a.U, a.NC * a.ntile_max);
+  if (b.u >= a.U) return;
+  const int r = b.item / a.ntile_max, tile = b.item % a.ntile_max;
+  const int s0 = r * a.C + tile * kTileTok;
+  const int len = min(kTileTok, min(a.T, (r + 1) * a.C) - s0);
+  if (len <= 0) return;                  // past the end of a ragged chunk
+  const long t = (b.u * a.NC + r) * a.ntile_max + tile;
+  const int njb = (a.dh + 31) / 32 * 2;
+  bwd_query_tile<G>(a, sm, b.u, r, len, b.u * a.T + s0,
+                    a.qaops + t * (G::NA_QRY * G::NIB * 1024),
+                    a.qbops + t * (G::NB_QRY * njb * 1024L));
 }
 
 // Bound by memory as the forward's.  Two workgroups per CU where their registers
@@ -594,7 +618,8 @@ __global__ void __launch_bounds__(256, 1) tile_bwd_token_kernel(TileBwdArgs a) {
 template <class G>
 __global__ void __launch_bounds__(256, G::FW == 0 || G::D == 64 ? 2 : 1)
     tile_bwd_state_kernel(TileBwdArgs a) {
-  constexpr int D = G::D, IH = G::IH, NMAT = G::NMAT, NF = G::NF, SEC = G::SEC, NA = G::NA_BWD;
+  constexpr int D = G::D, IH = G::IH, NMAT = G::NMAT, NF = G::NF, SEC = G::SEC;
+  constexpr int NA = G::NA_KEY + G::NA_QRY, NB = G::NB_KEY + G::NB_QRY;
   constexpr int BD = G::FW == 0 && D == 64 ? 3 : 1;
   constexpr int NV = (NA * IH * 64 + 255) / 256;   // staged 16-byte vectors per thread
   static_assert(NA * IH * 64 % 64 == 0, "whole waves of vectors");
@@ -647,8 +672,8 @@ __global__ void __launch_bounds__(256, G::FW == 0 || G::D == 64 ? 2 : 1)
   if (!a.init) {
     const float* car = a.carry + (u * a.NC + a.r) * 3;
     const float cw = car[0], cm = car[1], cb = car[2];
-    const char* const aop = a.aops + u * a.ntile_max * (long)NA * G::NIB * 1024;
-    const char* const bop = a.bops + u * a.ntile_max * (long)G::NB_BWD * njb * 1024;
+    const long tk = u * a.ntile_max;                            // the chunk's tiles
+    const long tq = a.qall ? (u * a.NC + a.r) * a.ntile_max : tk;
     // B operands BD tiles ahead (as many as two workgroups per CU leave
     // registers for), A operands two (one in flight, one in LDS)
     struct Stage {
@@ -659,18 +684,23 @@ __global__ void __launch_bounds__(256, G::FW == 0 || G::D == 64 ? 2 : 1)
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         const int e = tid + v * 256, x = e / (IH * 64), o = e % (IH * 64);
-        if (e < NA * IH * 64)
-          p.v[v] = reinterpret_cast<const u32x4*>(
-              aop + ((long)tile * NA + x) * G::NIB * 1024)[ib0 * 64 + o];
+        const char* src = x < G::NA_KEY
+                              ? a.aops + ((tk + tile) * G::NA_KEY + x) * (G::NIB * 1024)
+                              : a.qaops + ((tq + tile) * G::NA_QRY + x - G::NA_KEY) * (G::NIB * 1024);
+        if (e < NA * IH * 64) p.v[v] = reinterpret_cast<const u32x4*>(src)[ib0 * 64 + o];
       }
     };
-    using BFrags = bf16x8[G::NB_BWD];
+    using BFrags = bf16x8[NB];
     BFrags b0, b1, b2, b3;
     auto load_b = [&](BFrags& f, int tile) {
       if (tile >= a.ntile) return;
 #pragma unroll
-      for (int x = 0; x < G::NB_BWD; ++x)
-        f[x] = ld_frag(bop + (long)tile * G::NB_BWD * njb * 1024, x * njb + (mine ? jb : 0), lane);
+      for (int x = 0; x < NB; ++x) {
+        const char* src = x < G::NB_KEY
+                              ? a.bops + ((tk + tile) * G::NB_KEY + x) * (njb * 1024L)
+                              : a.qbops + ((tq + tile) * G::NB_QRY + x - G::NB_KEY) * (njb * 1024L);
+        f[x] = ld_frag(src, mine ? jb : 0, lane);
+      }
     };
     load_a(p0, 0);
     load_b(b0, 0);
@@ -681,7 +711,7 @@ __global__ void __launch_bounds__(256, G::FW == 0 || G::D == 64 ? 2 : 1)
     }
     // carry adjoints <Wb, W_0>, <Wb, M_0>, <Mb, M_0> of this workgroup's share
     {
-      const char* const w0 = a.wops + a.r * a.wslot + u * 3 * a.copy;
+      const char* const w0 = a.wops + a.r * a.wslot + u * a.wunit;
       const char* const m0 = a.mops + a.r * a.mslot + u * a.copy;
       float pcw = 0.0f, pcm = 0.0f, pcb = 0.0f;
       if (mine) {
@@ -822,12 +852,16 @@ hipError_t run(const TileBwdArgs& base, hipStream_t s) {
   a.r = a.NC - 1;
   hipLaunchKernelGGL(tile_bwd_state_kernel<StateShape<G>>, dim3((unsigned)gs), dim3(256), 0, s, a);
   a.init = 0;
+  if (a.qall)
+    hipLaunchKernelGGL(tile_bwd_query_kernel<G>, dim3((unsigned)tile_grid(a.U, a.NC * a.ntile_max)),
+                       dim3(256), 0, s, a);
   for (int r = a.NC - 1; r >= 0; --r) {
     a.r = r;
     a.last = r == 0;
     a.ntile = (std::min(a.C, a.T - r * a.C) + kTileTok - 1) / kTileTok;
-    hipLaunchKernelGGL(tile_bwd_token_kernel<G>, dim3((unsigned)tile_grid(a.U, 2 * a.ntile)),
-                       dim3(256), 0, s, a);
+    hipLaunchKernelGGL(tile_bwd_token_kernel<G>,
+                       dim3((unsigned)tile_grid(a.U, a.qall ? a.ntile : 2 * a.ntile)), dim3(256), 0,
+                       s, a);
     hipLaunchKernelGGL(tile_bwd_state_kernel<StateShape<G>>, dim3((unsigned)gs), dim3(256), 0, s,
                        a);
   }
@@ -835,6 +869,20 @@ hipError_t run(const TileBwdArgs& base, hipStream_t s) {
 }
 
 }  // namespace
+
+hipError_t launch_tile_bwd_query(const ChainConfig& cfg, const TileBwdArgs& a, hipStream_t s) {
+  const int nq = ((a.dh + 31) / 32 + 3) / 4;
+  const dim3 grid((unsigned)tile_grid(a.U, a.NC * a.ntile_max));
+#define E2TTT_TILE(FW, D, MAXQ)                                                                \
+  if (cfg.fw == FW && cfg.d == D && nq <= MAXQ) {                                              \
+    hipLaunchKernelGGL((tile_bwd_query_kernel<TileShape<FW, D, MAXQ>>), grid, dim3(256), 0, s, \
+                       a);                                                                     \
+    return hipGetLastError();                                                                  \
+  }
+#include "tile_variants.inc"
+#undef E2TTT_TILE
+  return hipErrorInvalidValue;
+}
 
 hipError_t launch_tile_bwd(const ChainConfig& cfg, const TileBwdArgs& a, hipStream_t s) {
   const int nq = ((a.dh + 31) / 32 + 3) / 4;   // blocks of 32 hidden columns per wave
@@ -856,16 +904,19 @@ bool tile_supported(const ChainConfig& cfg, int dh) {
 
 int tile_state_groups(int dh) { return ((dh + 31) / 32 * 2 + 3) / 4 * 2; }
 
-long tile_aop_bytes(const ChainConfig& cfg, bool backward) {
+long tile_aop_bytes(const ChainConfig& cfg, TileOps ops) {
   using G = TileShape<0, 64, 1>;
-  return (long)(backward ? G::NA_BWD : G::NA_FWD) * (cfg.d / 16) * 1024;
+  const long n = ops == kTileFwd ? G::NA_FWD : (ops == kTileBwdKey ? G::NA_KEY : G::NA_QRY);
+  return n * (cfg.d / 16) * 1024;
 }
 
-long tile_bop_bytes(const ChainConfig& cfg, int dh, bool backward) {
+long tile_bop_bytes(const ChainConfig& cfg, int dh, TileOps ops) {
   using G0 = TileShape<0, 64, 1>;
   using G1 = TileShape<1, 64, 1>;
-  const long n = cfg.fw == 0 ? (backward ? G0::NB_BWD : G0::NB_FWD)
-                             : (backward ? G1::NB_BWD : G1::NB_FWD);
+  const bool sw = cfg.fw != 0;
+  const long n = ops == kTileFwd      ? (sw ? G1::NB_FWD : G0::NB_FWD)
+                 : ops == kTileBwdKey ? (sw ? G1::NB_KEY : G0::NB_KEY)
+                                      : (sw ? G1::NB_QRY : G0::NB_QRY);
   return n * ((dh + 31) / 32 * 2) * 1024;
 }
 

@@ -58,11 +58,14 @@ struct TileShape {
   static constexpr int LDR = D + 4;              // [t][i] partial-sum rows (fp32)
   static constexpr int LDT = kTileTok + 4;       // quad rows of the transposing buffers
   // B operands of a tile: forward MLP dH as bf16 high and low parts, A; SwiGLU
-  // K^W dH and K^M dH of both matrices, A; backward A, dAh, Hh, then A_Q, Hb_Q
+  // K^W dH and K^M dH of both matrices, A; backward key side A, dAh, Hh, query
+  // side A_Q, Hb_Q
   static constexpr int NB_FWD = FW == 0 ? 3 : 5;
-  static constexpr int NB_BWD = FW == 0 ? 5 : 7;
+  static constexpr int NB_KEY = 2 + NF;
+  static constexpr int NB_QRY = 1 + NF;
   static constexpr int NA_FWD = 3;               // K^W dY, K^M dY, K
-  static constexpr int NA_BWD = 5;               // dY, Yh, K, Yb_Q, Q
+  static constexpr int NA_KEY = 3;               // dY, Yh, K
+  static constexpr int NA_QRY = 2;               // Yb_Q, Q
   static constexpr int RED = kTileTok * LDR;     // floats of one partial-sum buffer
   static constexpr int TI = kTileTok * LDD;      // elements of a [t][i] operand
   static constexpr int IT = (D / 4) * LDT * 4;   // elements of an [i][t] quad buffer

@@ -58,8 +58,8 @@ constexpr int kFwdRing = 16;
 template <class G>
 struct NetSeq {
   static constexpr int PER = 2 * G::NF * 2 * G::KD + G::NIB;
-  const bf16x8* rh;    // R copy, high part; the low part follows, then the T copy
-  long copy16;         // 16-byte vectors of a copy
+  const bf16x8* rh;    // R copy, high part; the low part follows
+  long copy16, t16;    // 16-byte vectors to the low part, to the T copy
   int dhb, w;
   __device__ __forceinline__ const bf16x8* operator()(int n) const {
     const int k = n / PER, e = n % PER;
@@ -69,7 +69,7 @@ struct NetSeq {
       const int b = e / RB, m = e % RB / (2 * G::KD), p = e % (2 * G::KD);
       return rh + (p & 1) * copy16 + ((m * 2 * dhb + 2 * q + b) * G::KD + (p >> 1)) * 64;
     }
-    return rh + 2 * copy16 + ((G::SEC * G::NIB + (e - 2 * RB)) * dhb + q) * 64;
+    return rh + t16 + ((G::SEC * G::NIB + (e - 2 * RB)) * dhb + q) * 64;
   }
 };
 // R fragments of the second-layer matrix (high, low per K-step).
@@ -99,7 +99,7 @@ __device__ void fwd_key_tile(const TileFwdArgs& a, FwdTileSmem<G>& sm, long u, i
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15, i0 = c * EPL;
   const int dhb = (a.dh + 31) / 32, njb = 2 * dhb;
   const bf16x8* const rh =
-      reinterpret_cast<const bf16x8*>(a.wops + a.slot * a.wslot + u * 3 * a.copy);
+      reinterpret_cast<const bf16x8*>(a.wops + a.slot * a.wslot + u * a.wunit);
   char* const bop = a.bops + (u * a.ntile_max + tile) * (long)G::NB_FWD * njb * 1024;
   char* const aop = a.aops + (u * a.ntile_max + tile) * (long)G::NA_FWD * G::NIB * 1024;
   const Bf* kp = static_cast<const Bf*>(a.k) + row0 * D;
@@ -111,7 +111,7 @@ __device__ void fwd_key_tile(const TileFwdArgs& a, FwdTileSmem<G>& sm, long u, i
 #pragma unroll
   for (int ib = 0; ib < G::NIB; ++ib) yacc[ib][0] = yacc[ib][1] = zero4();
   using Seq = NetSeq<G>;
-  FragRing<kFwdRing, Seq> ring(Seq{rh, a.copy / 16, dhb, w}, lane);
+  FragRing<kFwdRing, Seq> ring(Seq{rh, a.copy / 16, a.toff / 16, dhb, w}, lane);
   f32x4 d1[NF][G::MAXQ][2][2];
 #pragma unroll
   for (int k = 0; k < G::MAXQ; ++k) {
@@ -261,14 +261,14 @@ __device__ void fwd_key_tile(const TileFwdArgs& a, FwdTileSmem<G>& sm, long u, i
 }
 
 template <class G>
-__device__ void fwd_query_tile(const TileFwdArgs& a, FwdTileSmem<G>& sm, long u, int len,
+__device__ void fwd_query_tile(const TileFwdArgs& a, float* red, long u, int slot, int len,
                                long row0) {
   constexpr int D = G::D, EPL = G::EPL, NF = G::NF;
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15, i0 = c * EPL;
   const int dhb = (a.dh + 31) / 32;
   const bf16x8* const rh =
-      reinterpret_cast<const bf16x8*>(a.wops + a.slot * a.wslot + u * 3 * a.copy);
+      reinterpret_cast<const bf16x8*>(a.wops + slot * a.wslot + u * a.wunit);
   const Bf* qp = static_cast<const Bf*>(a.q) + row0 * D;
 
   bf16x8 xf[2][G::KD];
@@ -277,7 +277,7 @@ __device__ void fwd_query_tile(const TileFwdArgs& a, FwdTileSmem<G>& sm, long u,
 #pragma unroll
   for (int ib = 0; ib < G::NIB; ++ib) yacc[ib][0] = yacc[ib][1] = zero4();
   using Seq = NetSeq<G>;
-  FragRing<kFwdRing, Seq> ring(Seq{rh, a.copy / 16, dhb, w}, lane);
+  FragRing<kFwdRing, Seq> ring(Seq{rh, a.copy / 16, a.toff / 16, dhb, w}, lane);
 #pragma unroll
   for (int k = 0; k < G::MAXQ; ++k) {
     if (w + 4 * k >= dhb) break;
@@ -302,14 +302,14 @@ __device__ void fwd_query_tile(const TileFwdArgs& a, FwdTileSmem<G>& sm, long u,
     const bf16x8 f0 = join8(aq[0][0], aq[1][0]), f1 = join8(aq[0][1], aq[1][1]);
     second_layer<G>(yacc, ring, k * Seq::PER + 2 * NF * 2 * G::KD, f0, f1);
   }
-  reduce_waves<G>(yacc, sm.red, w, g, c);
+  reduce_waves<G>(yacc, red, w, g, c);
   const float inv_d = 1.0f / D;
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
     const int t = 16 * s + 4 * w + g;
     const bool ok = t < len;
     float y[EPL], x[EPL], f[EPL];
-    red_row<G>(y, sm.red, t, i0);
+    red_row<G>(y, red, t, i0);
     float sig = 1.0f;
     if (a.resln) {
       row_bf<EPL>(x, qp + (long)t * D + i0, ok);
@@ -357,7 +357,21 @@ __global__ void __launch_bounds__(256, 1) tile_fwd_token_kernel(TileFwdArgs a) {
   const int len = min(kTileTok, min(a.T, (a.r + 1) * a.C) - s0);
   const long row0 = b.u * a.T + s0;
   if (key) fwd_key_tile<G>(a, sm, b.u, tile, len, row0);
-  else fwd_query_tile<G>(a, sm, b.u, len, row0);
+  else fwd_query_tile<G>(a, sm.red, b.u, a.slot, len, row0);
+}
+
+// The query side alone, of chunks [r0, r0 + items / nt32) at once: what a chain
+// launch that leaves it out runs behind itself (chain_fwd.hip).
+template <class G>
+__global__ void __launch_bounds__(256, 1) tile_fwd_query_kernel(TileFwdArgs a) {
+  __shared__ __attribute__((aligned(16))) float red[2 * G::RED];
+  const TileBlock b = tile_block(blockIdx.x, a.U, a.items);
+  if (b.u >= a.U) return;
+  const int r = a.r + b.item / a.ntile_max;
+  const int s0 = r * a.C + b.item % a.ntile_max * kTileTok;
+  const int len = min(kTileTok, min(a.T, (r + 1) * a.C) - s0);
+  if (len <= 0) return;                  // past the end of a ragged chunk
+  fwd_query_tile<G>(a, red, b.u, a.keep ? r : r - a.r, len, b.u * a.T + s0);
 }
 
 // Bound by memory: the B operands, the state in and out and its operand copies
@@ -556,7 +570,7 @@ __global__ void __launch_bounds__(256, 1) tile_fwd_state_kernel(TileFwdArgs a) {
           st[at(0, m, ib)] = W[m][ib];
           st[at(1, m, ib)] = M[m][ib];
         }
-      char* const rh = a.wops + a.slot_next * a.wslot + u * 3 * a.copy;
+      char* const rh = a.wops + a.slot_next * a.wslot + u * a.wunit;
       char* const rl = rh + a.copy;
       char* const th = rl + a.copy;
       char* const mh = a.mops ? a.mops + a.slot_next * a.mslot + u * a.copy : nullptr;
@@ -613,6 +627,21 @@ hipError_t run(const TileFwdArgs& base, hipStream_t s) {
 }
 
 }  // namespace
+
+hipError_t launch_tile_fwd_query(const ChainConfig& cfg, TileFwdArgs a, int nchunks, hipStream_t s) {
+  const int nq = ((a.dh + 31) / 32 + 3) / 4;
+  a.items = nchunks * a.ntile_max;
+  const dim3 grid((unsigned)tile_grid(a.U, a.items));
+#define E2TTT_TILE(FW, D, MAXQ)                                                                \
+  if (cfg.fw == FW && cfg.d == D && nq <= MAXQ) {                                              \
+    hipLaunchKernelGGL((tile_fwd_query_kernel<TileShape<FW, D, MAXQ>>), grid, dim3(256), 0, s, \
+                       a);                                                                     \
+    return hipGetLastError();                                                                  \
+  }
+#include "tile_variants.inc"
+#undef E2TTT_TILE
+  return hipErrorInvalidValue;
+}
 
 hipError_t launch_tile_fwd(const ChainConfig& cfg, const TileFwdArgs& a, hipStream_t s) {
   const int nq = ((a.dh + 31) / 32 + 3) / 4;   // blocks of 32 hidden columns per wave

@@ -27,6 +27,8 @@ struct TileFwdArgs {
   float* zq;
   float* rq;
   long U, P, copy;      // copy: bytes of one operand copy of a unit
+  long wunit;           // bytes between units in wops
+  long toff;            // bytes from a unit's R high to its T copy
   long wslot, mslot;    // bytes of one slot
   int T, C, NC, dh, ntile_max;
   int keep;             // 1: one slot per chunk (saving), 0: one slot
@@ -36,7 +38,7 @@ struct TileFwdArgs {
   const float* ln_b;
   int H;
   // set per launch
-  int r, slot, slot_next, ntile, init, last;
+  int r, slot, slot_next, ntile, init, last, items;
 };
 
 struct TileBwdArgs {
@@ -65,10 +67,13 @@ struct TileBwdArgs {
   float* kmb;
   float* carryb;        // [slots][U][NC][3], one slot per state workgroup of a unit
   char* gops;           // [U][R of Wb | T of Wb | R of Mb | T of Mb]
-  char* aops;
+  char* aops;           // key side: [U][ntile_max][dY, Yh, K], [A, dAh, Hh..]
   char* bops;
+  char* qaops;          // query side: [U][NC or 1][ntile_max][Yb_Q, Q], [A_Q, Hb_Q..]
+  char* qbops;
+  int qall;             // 1: of every chunk, formed by one launch ahead
   float* ln_zbar;       // with the affine: adjoint of a e
-  long U, P, copy, wslot, mslot;
+  long U, P, copy, wunit, wslot, mslot;
   int T, C, NC, dh, ntile_max;
   int resln;
   const float* ln_a;
@@ -79,12 +84,18 @@ struct TileBwdArgs {
 
 // Whether the path has kernels for a net and its shape.
 bool tile_supported(const ChainConfig& cfg, int dh);
-// Bytes of one tile's A and B operands, of both directions.
-long tile_aop_bytes(const ChainConfig& cfg, bool backward);
-long tile_bop_bytes(const ChainConfig& cfg, int dh, bool backward);
+// Bytes of one tile's A and B operands: of the forward, of the backward's key
+// side, of its query side.
+enum TileOps { kTileFwd, kTileBwdKey, kTileBwdQuery };
+long tile_aop_bytes(const ChainConfig& cfg, TileOps ops);
+long tile_bop_bytes(const ChainConfig& cfg, int dh, TileOps ops);
 // State workgroups of a unit: the slots of carryb.
 int tile_state_groups(int dh);
 hipError_t launch_tile_fwd(const ChainConfig& cfg, const TileFwdArgs& a, hipStream_t s);
 hipError_t launch_tile_bwd(const ChainConfig& cfg, const TileBwdArgs& a, hipStream_t s);
+// The query sides alone, for a chain that leaves them out: the forward's of
+// chunks [a.r, a.r + nchunks), the backward's of all chunks (ntile_max tiles each).
+hipError_t launch_tile_fwd_query(const ChainConfig& cfg, TileFwdArgs a, int nchunks, hipStream_t s);
+hipError_t launch_tile_bwd_query(const ChainConfig& cfg, const TileBwdArgs& a, hipStream_t s);
 
 }  // namespace e2ttt
