@@ -59,8 +59,9 @@ struct Plan {
   long copy = 0, wunit = 0, wslot = 0, mslot = 0;
   int ntile_max = 0;
   size_t off_aop = 0, off_bop = 0, off_wops = 0, off_mops = 0;
-  // chain kernels that leave the query side out
+  // chain kernels that leave the query side out: when saving, when not
   bool qoff = false;
+  bool qoff0 = false;
   bool qall = false;      // token-tiled path: the backward's query side ahead
   int nslot = 0;          // chunks of a launch without saving
   long copy0 = 0, wunit0 = 0;   // its operand copies without saving
@@ -271,10 +272,13 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool chain_only = false
   pl.off_nx = pl.off_ntgt + (pl.post_norm ? align_up((size_t)U * pl.nrows * sizeof(float)) : 0);
   pl.off_ckpt = pl.off_nx +
                 (pl.post_norm ? align_up(ngroups * ns * 2 * d.d * sizeof(float)) : 0);
-  pl.qoff = !chain_only && leaves_query(d, pl);
+  pl.qoff0 = !chain_only && leaves_query(d, pl);
   pl.copy = (long)tile_copy_bytes(d);
   pl.wunit = 3 * pl.copy;
   pl.wslot = (long)U * pl.wunit;
+  // saving keeps every chunk's copies, for SwiGLU twice the memory of the chain
+  // alone: not above 16 GiB of them, so that the longest sequences still fit
+  pl.qoff = pl.qoff0 && pl.NC <= (16L << 30) / pl.wslot;
   // without saving the query side needs the first layer's R copies and the second
   // layer's T copy only, of the chunks of one launch: half of all (SwiGLU, with
   // half as much again per copy, a third), 12 at least, in up to 256 MB (each
@@ -289,7 +293,7 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool chain_only = false
   const long nrun = (pl.NC + pl.nslot - 1) / pl.nslot;
   pl.nslot = (int)((pl.NC + nrun - 1) / nrun);
   pl.off_wops0 = pl.off_ckpt;
-  pl.ws_bytes = pl.off_ckpt + (pl.qoff ? align_up((size_t)pl.nslot * wslot0) : 0);
+  pl.ws_bytes = pl.off_ckpt + (pl.qoff0 ? align_up((size_t)pl.nslot * wslot0) : 0);
   pl.ckpt_stride = chain_ckpt_bytes(pl.cfg);
   // with the normalisation the backward also reads the final state (one more block)
   pl.ckpt_nc = pl.NC + (pl.post_norm ? 1 : 0);
@@ -539,7 +543,7 @@ e2ttt_status run_forward(const e2ttt_desc* desc, bool chain_only, const float* l
     a.nxbuf = at<float>(workspace, pl.off_nx);
     a.norm_pre = save_for_backward ? at<float>(workspace, pl.off_npre) : nullptr;
   }
-  if (!pl.qoff) return finish(launch_chain_fwd(pl.cfg, a, s), s, sync);
+  if (!(save_for_backward ? pl.qoff : pl.qoff0)) return finish(launch_chain_fwd(pl.cfg, a, s), s, sync);
   // the chain over a run of chunks, then their query sides at once
   a.asave = nullptr;
   a.copy = save_for_backward ? pl.copy : pl.copy0;
