@@ -70,3 +70,30 @@ def test_state_in_place_over_several_launches():
     e2ttt.forward_static(cfg, *args, ws, ms, out, ws, ms)
     for n, a, b in zip(("out", "w_out", "m_out"), (out, ws, ms), ref):
         assert torch.equal(a, b), n
+
+
+def test_several_launches_under_capture():
+    # the launches, the clearing of their flags between and the query kernels as
+    # one graph: every replay equals the eager call
+    w = WL.WORKLOADS[1].with_(fw=1, B=1, H=2, T=300, d=64, dh=172, C=10, seed=4500)
+    cfg = config_of(w, flags=BARE)
+    t = to_dev(with_state(WL.make_inputs(w), 3, 1e-2), w.io)
+    args = t["q"], t["k"], t["v"], t["eta"], t["beta"], t["gamma"], t["w_in"], t["m_in"]
+    ref = e2ttt.forward(cfg, *args)[:3]
+    got = tuple(torch.empty_like(r) for r in ref)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        e2ttt.forward_static(cfg, *args, *got)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        e2ttt.forward_static(cfg, *args, *got)
+    for _ in range(4):
+        for g in got:
+            g.fill_(float("nan"))
+        graph.replay()
+        eager = e2ttt.forward(cfg, *args)[:3]
+        torch.cuda.synchronize()
+        for n, a, b, c in zip(("out", "w_out", "m_out"), got, eager, ref):
+            assert torch.equal(a, b) and torch.equal(b, c), n
