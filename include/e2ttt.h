@@ -35,8 +35,9 @@
  *   - For the wider nets (d = 64: GELU MLP with dh > 128, SwiGLU with
  *     dh > 64; d = 128: dh > 64) each unit is split over two to eight
  *     workgroups that swap partial sums through the workspace (or the
- *     backward scratch).
- *     Calls that share a workspace or scratch buffer must not run
+ *     backward scratch); those
+ *     kernels are launched cooperatively, so a call may wait for the whole
+ *     device.  Calls that share a workspace or scratch buffer must not run
  *     concurrently.
  *
  * Tensor layouts (row-major, C order):

@@ -18,7 +18,7 @@ using namespace e2ttt;
 
 constexpr size_t kAlign = 256;
 // Upper bound on workgroup groups (two to eight workgroups sharing a unit) of
-// one launch; more units are taken in turn by the same groups.
+// one cooperative launch; more units are taken in turn by the same groups.
 constexpr long kMaxPairs = 128;
 
 // Chunks of up to 512 tokens (the paper's setting); a chunk longer than the
@@ -388,7 +388,7 @@ e2ttt_status finish(hipError_t e, hipStream_t s, const unsigned* sync = nullptr)
   return E2TTT_OK;
 }
 
-// Pairs for one launch: what the buffers were sized for, capped by
+// Pairs for one cooperative launch: what the buffers were sized for, capped by
 // what the device holds at once.  0 when the device cannot hold eight pairs.
 long launch_pairs(const Plan& pl, bool backward) {
   return std::min(pl.npairs, chain_max_pairs(pl.cfg, backward));

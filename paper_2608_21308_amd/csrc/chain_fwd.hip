@@ -960,11 +960,17 @@ int max_blocks_per_cu() {
 
 template <class S, bool LONG, bool PN, bool QOFF>
 hipError_t launch_as(const ChainArgs& a, hipStream_t stream) {
-  // (several workgroups per unit: why a plain launch will do is in pair_xchg.h)
-  const long blocks = S::NS == 1 ? a.U : S::NS * a.npairs;
-  hipLaunchKernelGGL((chain_fwd_kernel<S, LONG, PN, QOFF>), dim3((unsigned)blocks), dim3(S::NT), 0,
-                     stream, a);
-  return hipGetLastError();
+  if constexpr (S::NS == 1) {
+    hipLaunchKernelGGL((chain_fwd_kernel<S, LONG, PN, QOFF>), dim3((unsigned)a.U), dim3(S::NT), 0,
+                       stream, a);
+    return hipGetLastError();
+  } else {   // (why not a plain launch: pair_xchg.h)
+    ChainArgs b = a;
+    void* args[] = {&b};
+    return hipLaunchCooperativeKernel((const void*)chain_fwd_kernel<S, LONG, PN, QOFF>,
+                                      dim3((unsigned)(S::NS * a.npairs)), dim3(S::NT), args, 0,
+                                      stream);
+  }
 }
 
 template <class S>

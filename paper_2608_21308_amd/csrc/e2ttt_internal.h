@@ -178,7 +178,7 @@ struct ChainConfig {
   int njb;    // 16-wide hidden blocks per wave
   int ntb;    // 16-row token blocks per chunk
   int bf;     // 1: bf16 MFMA operands and io; 0: fp32
-  int ns;     // workgroups per unit (1 to 8)
+  int ns;     // workgroups per unit (1, or 2 to 8 with a cooperative launch)
   int pn;     // 1: with the post-chunk normalisation of the fast weights
 };
 
@@ -215,7 +215,7 @@ int chain_bwd_blocks_per_cu_pn(const ChainConfig& cfg);
 hipError_t launch_apply(const ChainConfig& cfg, int fw, ApplyArgs a, hipStream_t stream);
 // Clears n words (a kernel, so that it may be captured in a graph).
 hipError_t launch_zero_words(unsigned* p, long n, hipStream_t stream);
-// Pairs of the chain kernel that the device holds at once (multiple of 8).
+// Pairs a cooperative launch of the chain kernel can hold at once (multiple of 8).
 long chain_max_pairs(const ChainConfig& cfg, bool backward);
 // Bytes of one checkpoint block (W or M of one unit's workgroup at one chunk start).
 long chain_ckpt_bytes(const ChainConfig& cfg);

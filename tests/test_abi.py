@@ -286,3 +286,11 @@ def test_long_chunks(lib):
     assert lib.e2ttt_chunk_forward(ctypes.byref(d), *([f] * 12), 1 << 40, 0, None) == 3
     assert lib.e2ttt_chunk_backward(ctypes.byref(d), *([f] * 9), 1 << 40, *([f] * 12),
                                     1 << 40, None) == 3
+
+
+def test_groups_are_launched_cooperatively(lib):
+    # units split over workgroups that wait for each other: with plain launches
+    # two streams' launches could hold each other's CUs, which no GPU test may
+    # provoke, so this looks at what the library calls
+    with open(e2ttt.LIB_PATH, "rb") as f:
+        assert b"hipLaunchCooperativeKernel" in f.read()

@@ -1,7 +1,8 @@
-"""Chain launches of several streams on the device at once: the ranks of a
-unit's workgroup group are started by plain launches, so groups of different
-launches share the CUs; every call must still end with its waits met and the
-results it gives when it runs alone, bit for bit."""
+"""Chain launches of several streams at once: the ranks of a unit's workgroup
+group wait for each other, so a launch must not start on CUs that another one's
+incomplete groups hold (the launches are cooperative, also inside a captured
+graph); every call must end with its waits met and the results it gives when it
+runs alone, bit for bit."""
 import pytest
 import torch
 
@@ -38,3 +39,33 @@ def test_concurrent_streams_equal_one_stream(fw, d, dh, C):
         s.synchronize()
         for a, b in zip(got, ref):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("fw,d,dh,C", [(0, 64, 256, 64), (1, 64, 172, 64)])
+def test_concurrent_graphs_equal_one_stream(fw, d, dh, C):
+    w = WL.WORKLOADS[1].with_(fw=fw, B=8, H=16, T=256, d=d, dh=dh, C=C, seed=4350 + dh)
+    cfg = config_of(w)
+    t = to_dev(WL.make_inputs(w, with_grads=False), w.io)
+    args = t["q"], t["k"], t["v"], t["eta"], t["beta"], t["gamma"], t["w_in"], None
+    ref = e2ttt.forward(cfg, *args)[:3]
+    runs = []
+    for _ in range(3):
+        s = torch.cuda.Stream()
+        got = [torch.empty_like(r) for r in ref]
+        ws = e2ttt.alloc_workspace(cfg, False)
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=s):
+            e2ttt.forward(cfg, *args, out=got[0], w_out=got[1], m_out=got[2], workspace=ws)
+        runs.append((s, got, ws, graph))
+    for _ in range(3):
+        for s, got, _, graph in runs:
+            with torch.cuda.stream(s):
+                for g in got:
+                    g.fill_(float("nan"))
+                graph.replay()
+        for s, got, ws, _ in runs:
+            with torch.cuda.stream(s):
+                assert e2ttt.wait_status(cfg, ws) == 0
+            for a, b in zip(got, ref):
+                assert torch.equal(a, b)
