@@ -57,7 +57,8 @@ struct TileShape {
   static constexpr int LDD = D + 4;              // [t][i] operand rows (bf16)
   static constexpr int LDR = D + 4;              // [t][i] partial-sum rows (fp32)
   static constexpr int LDT = kTileTok + 4;       // quad rows of the transposing buffers
-  // B operands of a tile: forward MLP dH as bf16 high and low parts, A; SwiGLU
+  // B operands of a tile: forward MLP dH (fp32, its upper and its lower 16 bits
+  // as two fragments, so that both transpose as bf16 ones do), A; SwiGLU
   // K^W dH and K^M dH of both matrices, A; backward key side A, dAh, Hh, query
   // side A_Q, Hb_Q
   static constexpr int NB_FWD = FW == 0 ? 3 : 5;
@@ -107,6 +108,20 @@ __device__ __forceinline__ bf16x8 join8(const bf16x4& a, const bf16x4& b) {
   return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 __device__ __forceinline__ bf16x4 cvt4(const f32x4& x) { return OpT<true>::cvt(x); }
+
+// The upper and lower 16 bits of four fp32 words, and back.
+__device__ __forceinline__ void word_halves(const f32x4& x, bf16x4& hi, bf16x4& lo) {
+  typedef __attribute__((ext_vector_type(8))) short s16x8;
+  const s16x8 w = __builtin_bit_cast(s16x8, x);
+  hi = __builtin_bit_cast(bf16x4, __builtin_shufflevector(w, w, 1, 3, 5, 7));
+  lo = __builtin_bit_cast(bf16x4, __builtin_shufflevector(w, w, 0, 2, 4, 6));
+}
+__device__ __forceinline__ f32x4 from_halves(const bf16x4& hi, const bf16x4& lo) {
+  typedef __attribute__((ext_vector_type(4))) short s16x4;
+  return __builtin_bit_cast(f32x4, __builtin_shufflevector(__builtin_bit_cast(s16x4, lo),
+                                                           __builtin_bit_cast(s16x4, hi), 0, 4, 1,
+                                                           5, 2, 6, 3, 7));
+}
 
 // One transposing LDS read: within each group of 16 lanes, lane c receives
 // element c mod 4 of the quads addressed by lanes 4 r + c / 4, r = 0..3.

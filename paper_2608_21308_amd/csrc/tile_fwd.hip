@@ -8,7 +8,8 @@
 // State kernel: W <- cw W + cm M + sum_t K^W_t G_t, M <- cb M + sum_t K^M_t G_t.
 // Operand precision is that of the chain kernels: W1 and the W2 of dA as bf16
 // high and low parts, the MLP's first-layer sums over high and low parts of
-// K_t dH, fp32 accumulation and fp32 state.
+// K_t dH (formed from the fp32 dH, which goes through memory whole), fp32
+// accumulation and fp32 state.
 #include <algorithm>
 
 #include "tile_common.h"
@@ -232,13 +233,10 @@ __device__ void fwd_key_tile(const TileFwdArgs& a, FwdTileSmem<G>& sm, long u, i
         f32x4 da[2];
         first_layer<G>(da, ring2, k * Seq2::PER + b * 2 * G::KD, xf);
         if constexpr (G::FW == 0) {
-          bf16x4 hi[2], lo[2];
+          bf16x4 hi[2], lo[2];   // the halves of the fp32 words
 #pragma unroll
-          for (int tb = 0; tb < 2; ++tb) {
-            const f32x4 dh = da[tb] * d1[0][k][b][tb];
-            hi[tb] = cvt4(dh);
-            lo[tb] = cvt4(dh - quad_f32(hi[tb]));
-          }
+          for (int tb = 0; tb < 2; ++tb)
+            word_halves(da[tb] * d1[0][k][b][tb], hi[tb], lo[tb]);
           st_frag(bop, jb, lane, tr_tok<G>(sm.tr[w], hi[0], hi[1], g, c));
           st_frag(bop, njb + jb, lane, tr_tok<G>(sm.tr[w], lo[0], lo[1], g, c));
         } else {
@@ -497,7 +495,7 @@ __global__ void __launch_bounds__(256, 1) tile_fwd_state_kernel(TileFwdArgs a) {
                               __builtin_shufflevector(f[1], f[1], 4, 5, 6, 7)};
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const f32x4 x = quad_f32(hh[h]) + quad_f32(hl[h]);
+          const f32x4 x = from_halves(hh[h], hl[h]);
           const f32x4 vw = *reinterpret_cast<const f32x4*>(&sk[par][0][16 * h + 4 * g]) * x;
           const f32x4 vm = *reinterpret_cast<const f32x4*>(&sk[par][1][16 * h + 4 * g]) * x;
           wh[h] = cvt4(vw);

@@ -52,3 +52,26 @@ def test_static_workspace_too_small_for_tiles_runs_the_chain():
     for n, a, b in zip(("out", "w_out", "m_out"), got, ref):
         a, b = a.float().cpu().numpy(), b.float().cpu().numpy()
         assert np.linalg.norm(a - b) <= 1e-2 * np.linalg.norm(b), n
+
+
+def test_first_layer_deltas_are_whole():
+    # with W1 = 0 the net's output, its LayerNorm row and dY are the same numbers
+    # on both paths (no rounding to bf16 can fall the other way), and dH = dY W2 / 2
+    # differs by the order of its fp32 sum at most.  The state sums then agree to
+    # fp32 rounding: 150 terms of 2^-24 with random signs, 8e-7 at most (measured
+    # 0).  dH rounded to two bf16 parts on its way through memory gave 3.2e-6.
+    w = WL.WORKLOADS[1].with_(B=4, H=16, T=150, d=128, dh=512, C=150, seed=4250)
+    cfg = config_of(w)
+    assert e2ttt.workspace_bytes(cfg, False) > e2ttt.STATIC_WORKSPACE_BYTES   # (static: the chain)
+    x = WL.make_inputs(w)
+    x["w_in"][..., :512 * 128] = 0.0
+    t = to_dev(x, w.io)
+    args = t["q"], t["k"], t["v"], t["eta"], t["beta"], t["gamma"], t["w_in"], None
+    tiles = e2ttt.forward(cfg, *args)[1:3]
+    chain = [torch.empty_like(r) for r in tiles]
+    e2ttt.forward_static(cfg, *args, torch.empty_like(t["q"]), *chain)
+    for n, a, b in zip(("w_out", "m_out"), tiles, chain):
+        a, b = a[..., :512 * 128].double(), b[..., :512 * 128].double()
+        err = float((a - b).norm() / b.norm())
+        print("first layer", n, "%.2e" % err, flush=True)
+        assert err <= 8e-7, (n, err)
