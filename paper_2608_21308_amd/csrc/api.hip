@@ -280,16 +280,25 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool chain_only = false
   // alone: not above 16 GiB of them, so that the longest sequences still fit
   pl.qoff = pl.qoff0 && pl.NC <= (16L << 30) / pl.wslot;
   // without saving the query side needs the first layer's R copies and the second
-  // layer's T copy only, of the chunks of one launch: half of all (SwiGLU, with
-  // half as much again per copy, a third), 12 at least, in up to 256 MB (each
-  // further launch costs some 28 us: the chain's start and end, its query sides)
+  // layer's T copy only, of the chunks of one launch.  Each further launch costs
+  // 28 us for the chain's start and end and its query sides, and 17 us more when
+  // it is cooperative.  Gain over the chain alone in one / two / three launches:
+  // 13 chunks 1.08 to 1.16 / 0.84 to 0.88 (MLP 256), 0.92 (SwiGLU 172); 32 chunks,
+  // 8 to 16 units 1.15 to 1.20 / 1.03 to 1.06 / SwiGLU 1.00 to 0.97; 32 units 1.12
+  // to 1.16 / 0.98 to 1.03.  So calls below 32 chunks and those above 16 units take
+  // all chunks at once, in up to 256 MB (65 chunks or more).  The others take two
+  // launches (SwiGLU with up to 8 units three: a third more per copy), whose copies
+  // stay below the backward's operands of the query side and, so that longer chunks
+  // never need less, below a call's with chunks of 512
   const long nmat = d.fw == E2TTT_FW_GELU_MLP ? 2 : 3;
   pl.copy0 = pl.copy / nmat * (nmat - 1);
   pl.wunit0 = 2 * pl.copy0 + pl.copy / nmat;
   const long wslot0 = (long)U * pl.wunit0;
   pl.ntile_max = (std::min(d.chunk, d.T) + kTileRows - 1) / kTileRows;
-  pl.nslot =
-      (int)std::min(pl.NC, std::max(12L, std::min((pl.NC + nmat - 1) / nmat, (256L << 20) / wslot0)));
+  const long fit = (256L << 20) / wslot0;
+  const long runs = nmat == 3 && pl.U <= 8 ? 3 : 2;
+  pl.nslot = (int)std::min(
+      pl.NC, pl.U > 16 ? fit : std::max(pl.NC < 32 ? 31L : 1L, std::min(fit, (pl.NC + runs - 1) / runs)));
   const long nrun = (pl.NC + pl.nslot - 1) / pl.nslot;
   pl.nslot = (int)((pl.NC + nrun - 1) / nrun);
   pl.off_wops0 = pl.off_ckpt;

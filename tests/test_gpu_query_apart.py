@@ -29,13 +29,15 @@ BARE, AFF, PN = e2ttt.FLAG_NO_RESIDUAL_LN, e2ttt.FLAG_LN_AFFINE, e2ttt.FLAG_POST
     (0, 64, 1, 2, 113, 16, 0),          # eight chunks, the last of one token
     (0, 100, 3, 3, 236, 33, 0),         # nine units, a second tile of one token
     (0, 128, 1, 1, 510, 64, BARE),      # whole tiles, the last chunk two tokens short
-    (0, 250, 1, 3, 127, 5, 0),          # two workgroups, 26 chunks: two launches
+    (0, 250, 1, 3, 127, 5, 0),          # two workgroups, 26 chunks
+    (0, 250, 1, 3, 167, 5, BARE),       # 34 chunks: two launches
     (0, 256, 2, 16, 90, 10, PN | BARE), # the most units
     (1, 64, 1, 2, 129, 16, AFF),
     (1, 100, 1, 3, 236, 33, BARE),
-    (1, 172, 1, 2, 121, 4, BARE),       # three workgroups, 31 chunks: three launches
+    (1, 172, 1, 2, 121, 4, BARE),       # three workgroups, 31 chunks
+    (1, 172, 1, 2, 130, 4, BARE),       # 33 chunks: three launches
     (1, 172, 1, 9, 110, 12, PN | AFF),
-    (1, 128, 1, 2, 142, 5, PN | AFF),   # 29 chunks: three launches, normalised
+    (1, 128, 1, 2, 142, 5, PN | AFF),   # 29 chunks, normalised
     (1, 64, 1, 2, 570, 70, PN | AFF),   # chunks of two chain tiles
 ])
 def test_query_side_apart(fw, dh, B, H, T, C, flags):
@@ -61,7 +63,7 @@ def test_query_side_apart(fw, dh, B, H, T, C, flags):
 
 def test_state_in_place_over_several_launches():
     # w_out over w_in: later launches read the state that the first one left
-    w = WL.WORKLOADS[1].with_(fw=0, B=1, H=2, T=300, d=64, dh=256, C=10, seed=4400)
+    w = WL.WORKLOADS[1].with_(fw=0, B=1, H=2, T=420, d=64, dh=256, C=10, seed=4400)
     cfg = config_of(w)
     t = to_dev(with_state(WL.make_inputs(w), 3, 1e-2), w.io)
     args = t["q"], t["k"], t["v"], t["eta"], t["beta"], t["gamma"]
@@ -75,7 +77,7 @@ def test_state_in_place_over_several_launches():
 def test_several_launches_under_capture():
     # the launches, the clearing of their flags between and the query kernels as
     # one graph: every replay equals the eager call
-    w = WL.WORKLOADS[1].with_(fw=1, B=1, H=2, T=300, d=64, dh=172, C=10, seed=4500)
+    w = WL.WORKLOADS[1].with_(fw=1, B=1, H=2, T=420, d=64, dh=172, C=10, seed=4500)
     cfg = config_of(w, flags=BARE)
     t = to_dev(with_state(WL.make_inputs(w), 3, 1e-2), w.io)
     args = t["q"], t["k"], t["v"], t["eta"], t["beta"], t["gamma"], t["w_in"], t["m_in"]
@@ -97,3 +99,47 @@ def test_several_launches_under_capture():
         torch.cuda.synchronize()
         for n, a, b, c in zip(("out", "w_out", "m_out"), got, eager, ref):
             assert torch.equal(a, b) and torch.equal(b, c), n
+
+
+# many units, whose launches take what 256 MB of copies hold (85 chunks of 32
+# units MLP 256, 68 SwiGLU 172, 85 of 64 units MLP 128): two and three launches
+@pytest.mark.parametrize("fw,dh,U,NC,C,flags", [
+    (0, 256, 32, 87, 2, 0),
+    (1, 172, 32, 140, 3, BARE),
+    (0, 128, 64, 171, 1, PN | BARE),
+])
+def test_several_launches_equal_one(fw, dh, U, NC, C, flags):
+    # saving runs all chunks in one launch; without saving, with the state in
+    # place, and as a graph (the launches and the clearing of their flags
+    # between): the same numbers
+    T = NC * C - (C > 1)
+    w = WL.WORKLOADS[1].with_(fw=fw, B=2, H=U // 2, T=T, d=64, dh=dh, C=C, seed=4600 + dh)
+    cfg = config_of(w, flags=flags)
+    t = to_dev(with_state(WL.make_inputs(w, with_grads=False), 3, 1e-2), w.io)
+    gates = t["q"], t["k"], t["v"], t["eta"], t["beta"], t["gamma"]
+    args = *gates, t["w_in"], t["m_in"]
+    mats = 2 if fw == 0 else 3
+    slot = U * (2 * (mats - 1) + 1) * ((dh + 31) // 32 * 32) * 64 * 2
+    assert 256 << 20 < NC * slot
+    ref = e2ttt.forward(cfg, *args, save_for_backward=True)[:3]
+    assert all(torch.isfinite(r.float()).all() for r in ref)
+    *got, ws = e2ttt.forward(cfg, *args)
+    assert e2ttt.wait_status(cfg, ws) == 0
+    for n, a, b in zip(("out", "w_out", "m_out"), got, ref):
+        assert torch.equal(a, b), n
+    st = t["w_in"].clone(), t["m_in"].clone()
+    out = e2ttt.forward(cfg, *gates, *st, w_out=st[0], m_out=st[1], workspace=ws)[0]
+    for n, a, b in zip(("out", "w_out", "m_out"), (out, *st), ref):
+        assert torch.equal(a, b), "in place: " + n
+    s = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=s):
+        e2ttt.forward(cfg, *args, out=got[0], w_out=got[1], m_out=got[2], workspace=ws)
+    for _ in range(3):
+        for g in got:
+            g.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        for n, a, b in zip(("out", "w_out", "m_out"), got, ref):
+            assert torch.equal(a, b), "graph: " + n

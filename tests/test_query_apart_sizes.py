@@ -24,3 +24,24 @@ def test_saved_copies_are_bounded(fw, dh, U):
     assert below[1] > 16 * GIB - slot and above[1] < below[1]
     assert above[2] < below[2] // 8                            # (the query's operands)
     assert above[0] - below[0] < GIB // 4                      # without saving: alike
+
+
+def slot_bytes(fw, dh, U):
+    # one chunk's copies without saving
+    mats = 2 if fw == 0 else 3
+    return U * (2 * (mats - 1) + 1) * ((dh + 31) // 32 * 32) * 64 * 2
+
+
+@pytest.mark.parametrize("fw,dh,U,NC", [(0, 256, 8, 13), (0, 256, 8, 31), (0, 256, 32, 64),
+                                        (1, 172, 16, 31), (0, 120, 64, 40)])
+def test_one_launch_where_a_second_would_cost_more(fw, dh, U, NC):
+    # (a launch too many costs as much as the query sides of some twenty chunks)
+    slot = slot_bytes(fw, dh, U)
+    assert NC * slot <= 256 << 20
+    assert sizes(fw, dh, U, 64 * NC)[0] - sizes(fw, dh, U, 64 * 8)[0] >= (NC - 8) * slot
+
+
+@pytest.mark.parametrize("fw,dh,U,NC", [(0, 256, 8, 32), (1, 172, 16, 128), (0, 256, 16, 512)])
+def test_few_units_and_many_chunks_need_no_more_than_the_backward(fw, dh, U, NC):
+    free, _, scratch = sizes(fw, dh, U, 64 * NC)
+    assert free <= scratch and free <= (256 << 20) + NC * 64 * U * 64
