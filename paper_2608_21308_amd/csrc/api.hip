@@ -117,38 +117,90 @@ size_t tile_copy_bytes(const e2ttt_desc& d) {
   return (size_t)(d.fw == E2TTT_FW_GELU_MLP ? 2 : 3) * ((d.dh + 31) / 32 * 32) * d.d * 2;
 }
 
-// Whether the token-tiled path runs the call: chunks of more than 64 tokens, where an estimate of a forward chunk's time (us) says that
-// it is the faster path by a margin.  The estimates are fitted to both paths'
-// times over 11 nets (head dims 64 and 128, dh 64 to 512), 2 to 128 units and
-// chunks of 64 to 512 tokens; with the margin of 1.2 the path never lost in
-// them, forward or training step, and gained 1.6x in the geometric mean.
-//   chain: a chunk's tiles one after the other, as many units at once as the
-//     device holds workgroups for.  A 64-token tile at head dim 64 takes 9.7 us
-//     (SwiGLU 11.7), a 32-token tile at head dim 128 12 to 16 us (SwiGLU to 20),
-//     growing with the ranks that swap sums.
-//   tiles: two launches (12 us), the state kernel's walk over the tokens, the
-//     state's way through memory, and the work of all tokens, which the whole
-//     device shares.
-// Measured, chain over tiles, forward: head dim 64, dh 256, C = 128: 8 units
-// 1.3, 32 units 1.1, 96 units 0.5; C = 512: 2.8, 2.0, 0.9; head dim 128, dh 512,
-// C = 128: 8 units 1.9, 128 units 1.5, C = 512: 4.9, 2.7.
-bool takes_tiles(const e2ttt_desc& d, const Plan& pl) {
-  const int len = std::min(d.chunk, d.T), rows = 16 * pl.cfg.ntb;
-  // (at head dim 128 chunks of 33 to 64 tokens gained 1.0x to 1.3x and their
-  // saved operand copies, one set per chunk, took half as much memory again)
-  if (!pl.cfg.bf || pl.post_norm || len <= 64 || !tile_supported(pl.cfg, d.dh)) return false;
-  const double U = (double)pl.U;
-  const int ns = pl.cfg.ns;
-  const bool sw = d.fw == E2TTT_FW_SWIGLU;
+// Whether the chain leaves the query side to kernels over all chunks (forward:
+// the net at W_0 for the chunk's q, its LayerNorm and out; backward: dq and the
+// operands of the query's terms of dW_0).  In the chain they cost a fifth of a
+// chunk's time on the few CUs it uses; apart they use the whole device, but W_0
+// goes through memory as operand copies.  Time of the chain alone over this,
+// head dim 64, C = 64 (C = 16 alike), 8 / 32 / 128 chunks:
+//   forward  MLP 256:    8 units 1.11 1.12 1.19, 32 units 1.06 1.05, 64 units 0.99 0.98
+//            MLP 120:    1.13 1.15 1.23, 1.10 1.11, 64 units 1.07 1.05
+//            SwiGLU 172: 1.15 1.10 1.22, 1.11 1.03, 64 units 1.02 0.95
+//            SwiGLU 64:  1.14 1.09 1.22, 1.11 1.05, 64 units 1.07 0.99
+//   training MLP 256:    1.10 1.16, 1.06 1.09, 64 units 0.98 0.99
+//   step     MLP 120:    1.05 1.18 1.18, 1.08 1.14, 64 units 1.04 1.07
+//            SwiGLU 172: 1.14 1.20 1.20, 1.09 1.13, 64 units 1.03 1.03
+// and with 4 chunks 0.96 to 1.07 (the launches).
+bool leaves_query(const e2ttt_desc& d, const Plan& pl) {
+  const bool mlp = d.fw == E2TTT_FW_GELU_MLP;
+  if (!pl.cfg.bf || d.d != 64 || pl.NC < 8) return false;
+  return pl.U <= (mlp && pl.cfg.ns == 1 ? 64 : 32);
+}
+
+// Times (us) that the path rule below is made of.
+struct PathTimes {
+  double tok, tokq;      // a wave of token workgroups; per 128 hidden columns
+  double tokb;           // 256 token workgroups, per 32 hidden columns (operand loads)
+  double st, stn;        // a wave of state workgroups; per 32 tokens of the chunk
+  double tiles;          // a call on the tiles
+  double chain, rank;    // a token tile of the chain; per further workgroup of a unit
+  double one, many;      // a call on the chain, one workgroup per unit, several
+};
+// [saving: forward and backward][net][head dim 64, 128]
+constexpr PathTimes kPathTimes[2][2][2] = {
+    {{{0.28, 1.37, 0.21, 8.40, 0.73, 10.3, 8.66, 0.68, 10, 33},
+      {4.59, 2.48, 0.23, 8.64, 0.75, 11.2, 10.89, 0.65, 10, 33}},
+     {{0.03, 2.13, 0.42, 9.84, 0.66, 10.8, 10.03, 1.26, 10, 33},
+      {3.78, 2.61, 1.03, 12.77, 0.59, 13.8, 14.87, 0.93, 10, 33}}},
+    {{{3.10, 5.98, 0.49, 16.26, 2.15, 32.4, 27.09, 0.58, 28, 85},
+      {10.68, 8.08, 0.76, 22.29, 1.55, 33.6, 29.70, 1.31, 28, 85}},
+     {{3.64, 6.06, 1.18, 20.97, 1.65, 30.6, 34.09, 1.79, 28, 85},
+      {8.41, 9.40, 2.54, 32.81, 1.46, 38.2, 47.49, 1.02, 28, 85}}}};
+
+// Waves of n workgroups over 256 CUs, one per CU, at least one: half way to
+// whole ones, since some kernels have a second workgroup of a CU to fill with.
+double waves(double n) { return 0.5 * (std::ceil(n / 256) + std::max(1.0, n / 256)); }
+
+// Whether the token-tiled path runs the call: chunks of more than 64 tokens,
+// where an estimate of both paths' times says that it is the faster one.
+//   chain: a chunk's token tiles one after the other, as many units at once as
+//     the device holds workgroups for; an eighth less where it leaves the query
+//     side out.
+//   tiles: per chunk the token kernel and the state kernel in waves of workgroups
+//     (units are dealt to the XCDs in eights).
+// The constants are a least-squares fit to the times of 9,289 calls on the tiles
+// and 10,704 on the chain: both nets and head dims, every width, 1 to 520 units,
+// chunks of 65 to 512 tokens, up to fourteen chunks, the last one ragged; nine
+// tenths of the estimates of any net lie within 0.82 and 1.18 of the time.  With
+// the margin no timed call lost more than 4 % to the chain alone on the tiles (one
+// 5 % to a chain that leaves its query side out); without it 2 % of them did, the
+// worst by 11 %.  Chain over tiles, forward / step, head dim 64, dh 256, C = 128: 8
+// units 1.3 / 1.5, 128 units 0.5 / 0.6; C = 512: 2.9 / 3.1, 0.8 / 0.8; head dim
+// 128, dh 512, C = 128: 8 units 2.0 / 2.2, 128 units 1.5 / 1.6; dh 33, C = 68: 107
+// units 0.86 / 0.92.
+bool takes_tiles(const e2ttt_desc& d, const Plan& pl, bool saving) {
+  const int rows = 16 * pl.cfg.ntb, ns = pl.cfg.ns;
+  // (at head dim 128 shorter chunks are left on the chain: their gain was 1.15 to
+  // 2.0 where this estimate took them, for twice the saved memory per token)
+  if (!pl.cfg.bf || pl.post_norm || std::min(d.chunk, d.T) <= 64 || !tile_supported(pl.cfg, d.dh))
+    return false;
+  const PathTimes& t = kPathTimes[saving][d.fw == E2TTT_FW_SWIGLU][d.d == 128];
   const double held = ns > 1 ? 256 / ns / 8 * 8 : 256;   // units that run at once (256 CUs)
-  const double tile_us = d.d == 64 ? (sw ? 11.7 : 9.7) : (sw ? 14.0 + 0.7 * ns : 12.0 + 0.5 * ns);
-  const double chain_us = std::ceil(U / held) * ((len + rows - 1) / rows) * tile_us;
-  const double params = (double)(sw ? 3 : 2) * d.d * d.dh;
-  const double tiles_us = 12.0 + 0.017 * len + 3.7e-6 * U * params +
-                          U * len * (0.2e-3 * d.d / 64 +
-                                     // (four waves take whole blocks of 32 columns)
-                                     1.07e-3 * params / 32768 * std::max(1.0, 128.0 / d.dh));
-  return 1.2 * tiles_us < chain_us;
+  const double units = (double)(pl.U >= 8 ? (pl.U + 7) / 8 * 8 : pl.U);
+  const double state_waves = waves(units * tile_state_groups(d.dh));
+  const int blocks = (d.dh + 31) / 32, quarters = (blocks + 3) / 4;
+  const double chain_tile = std::ceil(pl.U / held) * (t.chain + t.rank * (ns - 1)) *
+                            (leaves_query(d, pl) ? 0.87 : 1.0);
+  double tiles_us = t.tiles, chain_us = ns > 1 ? t.many : t.one;
+  const int whole = d.T / d.chunk, rest = d.T % d.chunk;
+  for (int k = 0; k < 2; ++k) {
+    const int len = k == 0 ? d.chunk : rest, n = k == 0 ? whole : (rest > 0 ? 1 : 0);
+    const int nt = (len + kTileRows - 1) / kTileRows;
+    tiles_us += n * (waves(units * 2 * nt) * (t.tok + t.tokq * quarters) +
+                     units * 2 * nt / 256 * t.tokb * blocks + state_waves * (t.st + t.stn * nt));
+    chain_us += n * ((len + rows - 1) / rows) * chain_tile;
+  }
+  return 1.08 * tiles_us < chain_us;
 }
 
 // Layout of the token-tiled path: one operand copy set of W per chunk when
@@ -161,7 +213,8 @@ void tile_plan(const e2ttt_desc& d, Plan& pl, size_t tok, size_t chk) {
   pl.wslot = (long)U * pl.wunit;
   pl.mslot = (long)U * pl.copy;
   pl.ntile_max = (std::min(d.chunk, d.T) + kTileRows - 1) / kTileRows;
-  pl.off_state = pl.off_carry + align_up(chk);
+  // (the status word of a call on the chain, which the other kind of call may be)
+  pl.off_state = pl.off_sync + kAlign;
   // the query side of all chunks at once where one chunk's tiles leave CUs idle
   pl.qall = pl.U * pl.ntile_max <= 128;
   pl.off_aop = pl.off_state + align_up(U * 4 * pl.copy);   // W and M, fp32
@@ -191,29 +244,10 @@ void tile_plan(const e2ttt_desc& d, Plan& pl, size_t tok, size_t chk) {
       pl.off_apart + (pl.affine ? align_up(U * nb * 2 * d.d * sizeof(float)) : 0);
 }
 
-// Whether the chain leaves the query side to kernels over all chunks (forward:
-// the net at W_0 for the chunk's q, its LayerNorm and out; backward: dq and the
-// operands of the query's terms of dW_0).  In the chain they cost a fifth of a
-// chunk's time on the few CUs it uses; apart they use the whole device, but W_0
-// goes through memory as operand copies.  Time of the chain alone over this,
-// head dim 64, C = 64 (C = 16 alike), 8 / 32 / 128 chunks:
-//   forward  MLP 256:    8 units 1.11 1.12 1.19, 32 units 1.06 1.05, 64 units 0.99 0.98
-//            MLP 120:    1.13 1.15 1.23, 1.10 1.11, 64 units 1.07 1.05
-//            SwiGLU 172: 1.15 1.10 1.22, 1.11 1.03, 64 units 1.02 0.95
-//            SwiGLU 64:  1.14 1.09 1.22, 1.11 1.05, 64 units 1.07 0.99
-//   training MLP 256:    1.10 1.16, 1.06 1.09, 64 units 0.98 0.99
-//   step     MLP 120:    1.05 1.18 1.18, 1.08 1.14, 64 units 1.04 1.07
-//            SwiGLU 172: 1.14 1.20 1.20, 1.09 1.13, 64 units 1.03 1.03
-// and with 4 chunks 0.96 to 1.07 (the launches).
-bool leaves_query(const e2ttt_desc& d, const Plan& pl) {
-  const bool mlp = d.fw == E2TTT_FW_GELU_MLP;
-  if (!pl.cfg.bf || d.d != 64 || pl.NC < 8) return false;
-  return pl.U <= (mlp && pl.cfg.ns == 1 ? 64 : 32);
-}
-
-// Plan of a descriptor; with chain_only, of the chain kernels also where the
-// token-tiled path would be taken.
-e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool chain_only = false) {
+// Plan of a descriptor for calls that save for the backward (and the backward)
+// or do not: the two may take different paths.  With chain_only, of the chain
+// kernels whatever the path.
+e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool saving, bool chain_only = false) {
   if (!desc) return E2TTT_ERR_NULL_ARG;
   const e2ttt_desc& d = *desc;
   if (d.B < 1 || d.H < 1 || d.T < 1 || d.d < 1 || d.dh < 1 || d.chunk < 1)
@@ -241,20 +275,17 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool chain_only = false
   const size_t chk = (size_t)U * pl.NC * 3 * sizeof(float);
   pl.affine = (d.flags & E2TTT_FLAG_LN_AFFINE) != 0;
   pl.post_norm = (d.flags & E2TTT_FLAG_POST_NORM) != 0;
-  pl.tile = !chain_only && takes_tiles(d, pl);
+  pl.tile = !chain_only && takes_tiles(d, pl, saving);
+  pl.off_km = align_up(tok);
+  pl.off_carry = pl.off_km + align_up(tok);
+  pl.off_sync = pl.off_carry + align_up(chk);
   if (pl.tile) {
-    pl.off_km = align_up(tok);
-    pl.off_carry = pl.off_km + align_up(tok);
     tile_plan(d, pl, tok, chk);
     return E2TTT_OK;
   }
   const long ns = pl.cfg.ns;
   pl.npairs = (ns > 1) ? std::min((U + 7) / 8 * 8, kMaxPairs) : 0;
   const size_t sync_b = (ns > 1) ? (size_t)sync_words(pl.npairs, (int)ns) * sizeof(unsigned) : 0;
-  pl.off_kw = 0;
-  pl.off_km = align_up(tok);
-  pl.off_carry = pl.off_km + align_up(tok);
-  pl.off_sync = pl.off_carry + align_up(chk);
   pl.off_xbuf = pl.off_sync + align_up(sync_b);
   const int cm_rows = 16 * pl.cfg.ntb;
   pl.tpc = (d.chunk > cm_rows) ? (d.chunk + cm_rows - 1) / cm_rows : 1;
@@ -449,7 +480,7 @@ namespace e2ttt {
 
 size_t chain_workspace_bytes(const e2ttt_desc* desc) {
   Plan pl;
-  return make_plan(desc, pl, true) == E2TTT_OK ? pl.ws_bytes : 0;
+  return make_plan(desc, pl, false, true) == E2TTT_OK ? pl.ws_bytes : 0;
 }
 
 e2ttt_status run_forward(const e2ttt_desc* desc, bool chain_only, const float* ln_weight,
@@ -459,7 +490,7 @@ e2ttt_status run_forward(const e2ttt_desc* desc, bool chain_only, const float* l
                          float* m_out, void* workspace, size_t workspace_bytes,
                          int save_for_backward, void* stream) {
   Plan pl;
-  e2ttt_status st = make_plan(desc, pl, chain_only);
+  e2ttt_status st = make_plan(desc, pl, save_for_backward != 0, chain_only);
   if (st != E2TTT_OK) return st;
   if (!q || !k || !v || !eta || !beta || !w_in || !out || !w_out || !m_out || !workspace)
     return E2TTT_ERR_NULL_ARG;
@@ -476,7 +507,7 @@ e2ttt_status run_forward(const e2ttt_desc* desc, bool chain_only, const float* l
   float* carry = at<float>(workspace, pl.off_carry);
   if (pl.tile) {
     CoeffFwdArgs c{eta, beta, gamma, kw, km, carry, (int)pl.T, desc->chunk, (int)pl.NC,
-                   pl.U * pl.NC, nullptr, 0, averaged(desc)};
+                   pl.U * pl.NC, at<unsigned>(workspace, pl.off_sync), 1, averaged(desc)};
     hipError_t e = launch_coeff_fwd(c, s);
     if (e != hipSuccess) return E2TTT_ERR_HIP;
     TileFwdArgs a{};
@@ -597,18 +628,21 @@ extern "C" {
 
 size_t e2ttt_param_count(const e2ttt_desc* desc) {
   Plan pl;
-  return make_plan(desc, pl) == E2TTT_OK ? (size_t)pl.P : 0;
+  return make_plan(desc, pl, false) == E2TTT_OK ? (size_t)pl.P : 0;
 }
 
 size_t e2ttt_workspace_bytes(const e2ttt_desc* desc, int save_for_backward) {
   Plan pl;
-  if (make_plan(desc, pl) != E2TTT_OK) return 0;
-  return save_for_backward ? pl.ws_bytes_save : pl.ws_bytes;
+  if (make_plan(desc, pl, false) != E2TTT_OK) return 0;
+  const size_t free_bytes = pl.ws_bytes;
+  if (!save_for_backward) return free_bytes;
+  if (make_plan(desc, pl, true) != E2TTT_OK) return 0;
+  return std::max(pl.ws_bytes_save, free_bytes);   // (a saving workspace serves either call)
 }
 
 size_t e2ttt_backward_scratch_bytes(const e2ttt_desc* desc) {
   Plan pl;
-  if (make_plan(desc, pl) != E2TTT_OK) return 0;
+  if (make_plan(desc, pl, true) != E2TTT_OK) return 0;
   return pl.scratch_bytes;
 }
 
@@ -629,7 +663,7 @@ e2ttt_status e2ttt_chunk_coeffs(const e2ttt_desc* desc, const float* eta, const 
                                 const float* gamma, float* kw, float* km, float* carry,
                                 void* stream) {
   Plan pl;
-  e2ttt_status st = make_plan(desc, pl);
+  e2ttt_status st = make_plan(desc, pl, false);
   if (st != E2TTT_OK) return st;
   if (!eta || !beta || !kw || !km || !carry) return E2TTT_ERR_NULL_ARG;
   CoeffFwdArgs c{eta, beta, gamma, kw, km, carry, (int)pl.T, desc->chunk, (int)pl.NC,
@@ -646,7 +680,7 @@ e2ttt_status e2ttt_apply(const e2ttt_desc* desc, const void* q, const float* w, 
 e2ttt_status e2ttt_apply_ln(const e2ttt_desc* desc, const float* ln_weight, const float* ln_bias,
                             const void* q, const float* w, void* out, void* stream) {
   Plan pl;
-  e2ttt_status st = make_plan(desc, pl);
+  e2ttt_status st = make_plan(desc, pl, false);
   if (st != E2TTT_OK) return st;
   if (!q || !w || !out) return E2TTT_ERR_NULL_ARG;
   st = check_affine(pl, ln_weight, ln_bias, false, nullptr, nullptr);
@@ -714,7 +748,7 @@ e2ttt_status e2ttt_chunk_backward_ln(const e2ttt_desc* desc, const float* ln_wei
                                      float* d_m_in, float* d_ln_weight, float* d_ln_bias,
                                      void* scratch, size_t scratch_bytes, void* stream) {
   Plan pl;
-  e2ttt_status st = make_plan(desc, pl);
+  e2ttt_status st = make_plan(desc, pl, true);
   if (st != E2TTT_OK) return st;
   st = check_affine(pl, ln_weight, ln_bias, true, d_ln_weight, d_ln_bias);
   if (st != E2TTT_OK) return st;
@@ -859,13 +893,16 @@ e2ttt_status e2ttt_chunk_backward_ln(const e2ttt_desc* desc, const float* ln_wei
 
 e2ttt_status e2ttt_wait_status(const e2ttt_desc* desc, const void* workspace,
                                const void* scratch, void* stream) {
-  Plan pl;
-  e2ttt_status st = make_plan(desc, pl);
+  Plan pl, plf;   // of saving calls and the backward, of the others
+  e2ttt_status st = make_plan(desc, pl, true);
+  if (st == E2TTT_OK) st = make_plan(desc, plf, false);
   if (st != E2TTT_OK) return st;
   if (!workspace && !scratch) return E2TTT_ERR_NULL_ARG;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (hipStreamSynchronize(s) != hipSuccess) return E2TTT_ERR_HIP;
-  if (pl.cfg.ns == 1 || pl.tile) return E2TTT_OK;   // no waits between workgroups
+  if (pl.cfg.ns == 1) return E2TTT_OK;   // no waits between workgroups
+  if (pl.tile && plf.tile) workspace = nullptr;
+  if (pl.tile) scratch = nullptr;
   unsigned word[2] = {0u, 0u};
   if (workspace && hipMemcpy(&word[0], at<unsigned>(workspace, pl.off_sync), sizeof(unsigned),
                              hipMemcpyDeviceToHost) != hipSuccess)

@@ -11,6 +11,7 @@ import torch
 
 from paper_2608_21308_amd import e2ttt, workloads as WL
 from tests.gpu_util import TOL, config_of, to_dev
+from tests.path_util import takes_tiles
 from tests.test_gpu_backward import errors as berrors, gpu_fwd_bwd, oracle_bwd, with_state_inputs
 
 pytestmark = pytest.mark.gpu
@@ -30,6 +31,7 @@ pytestmark = pytest.mark.gpu
 def test_tiles_forward_backward(fw, d, dh, B, H, T, C, flags):
     w = WL.WORKLOADS[1].with_(fw=fw, B=B, H=H, T=T, d=d, dh=dh, C=C, backward=True,
                               seed=4100 + T + dh)
+    assert takes_tiles(config_of(w, flags=flags), True)
     x = with_state_inputs(WL.make_inputs(w), 5, 1e-2)
     errs = berrors(gpu_fwd_bwd(w, x, flags), oracle_bwd(w, x, flags), C=C)
     print("tiles fw=%d d=%d dh=%d U=%d T=%d C=%d" % (fw, d, dh, B * H, T, C),
@@ -75,3 +77,31 @@ def test_first_layer_deltas_are_whole():
         err = float((a - b).norm() / b.norm())
         print("first layer", n, "%.2e" % err, flush=True)
         assert err <= 8e-7, (n, err)
+
+
+def test_saving_and_other_calls_on_different_paths_share_a_workspace():
+    # a shape whose saving call takes the one path and whose other call the other:
+    # on one buffer in turn, each reports its own status and both agree to the
+    # rounding of the two summation orders
+    cfgs = (e2ttt.Config(B=1, H=U, T=5 * C // 2, d=64, dh=dh, chunk=C, fw=fw, io=e2ttt.DT_BF16)
+            for fw, dh in ((0, 256), (1, 172)) for U in range(8, 130, 8) for C in (75, 100, 128, 300))
+    cfg = next(c for c in cfgs if takes_tiles(c, True) != takes_tiles(c, False))
+    w = WL.WORKLOADS[1].with_(fw=cfg.fw, B=1, H=cfg.H, T=cfg.T, d=64, dh=cfg.dh, C=cfg.chunk,
+                              backward=True, seed=4260)
+    t = to_dev(WL.make_inputs(w, with_grads=True), w.io)
+    args = t["q"], t["k"], t["v"], t["eta"], t["beta"], t["gamma"], t["w_in"], None
+    ws = e2ttt.alloc_workspace(cfg, True)
+    scratch = torch.empty(e2ttt.backward_scratch_bytes(cfg), dtype=torch.uint8, device="cuda")
+    ws.fill_(255)
+    scratch.fill_(255)
+    outs = []
+    for saving in (False, True, False):
+        outs.append(e2ttt.forward(cfg, *args, workspace=ws, save_for_backward=saving)[:3])
+        assert e2ttt.wait_status(cfg, ws) == 0
+        if saving:
+            e2ttt.backward(cfg, *args, ws, t["d_out"], scratch=scratch)
+            assert e2ttt.wait_status(cfg, ws, scratch) == 0
+    for a, b, c in zip(*outs):
+        assert torch.equal(a, c)
+        a, b = a.double(), b.double()
+        assert float((a - b).norm()) <= 1e-2 * float(b.norm())
