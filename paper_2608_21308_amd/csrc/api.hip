@@ -62,7 +62,6 @@ struct Plan {
   // chain kernels that leave the query side out: when saving, when not
   bool qoff = false;
   bool qoff0 = false;
-  bool qall = false;      // token-tiled path: the backward's query side ahead
   int nslot = 0;          // chunks of a launch without saving
   long copy0 = 0, wunit0 = 0;   // its operand copies without saving
   size_t off_wops0 = 0, off_qaop = 0, off_qbop = 0;
@@ -215,8 +214,6 @@ void tile_plan(const e2ttt_desc& d, Plan& pl, size_t tok, size_t chk) {
   pl.ntile_max = (std::min(d.chunk, d.T) + kTileRows - 1) / kTileRows;
   // (the status word of a call on the chain, which the other kind of call may be)
   pl.off_state = pl.off_sync + kAlign;
-  // the query side of all chunks at once where one chunk's tiles leave CUs idle
-  pl.qall = pl.U * pl.ntile_max <= 128;
   pl.off_aop = pl.off_state + align_up(U * 4 * pl.copy);   // W and M, fp32
   pl.off_bop = pl.off_aop + align_up(U * pl.ntile_max * tile_aop_bytes(pl.cfg, kTileFwd));
   pl.off_wops = pl.off_bop + align_up(U * pl.ntile_max * tile_bop_bytes(pl.cfg, d.dh, kTileFwd));
@@ -233,11 +230,11 @@ void tile_plan(const e2ttt_desc& d, Plan& pl, size_t tok, size_t chk) {
   pl.off_bstate = pl.off_carryb + align_up(tile_state_groups(d.dh) * chk);
   pl.off_gops = pl.off_bstate + align_up(U * 4 * pl.copy);
   pl.off_baop = pl.off_gops + align_up(U * 4 * pl.copy);
-  const size_t nt = U * pl.ntile_max, ntq = nt * (pl.qall ? pl.NC : 1);
+  const size_t nt = U * pl.ntile_max;
   pl.off_bbop = pl.off_baop + align_up(nt * tile_aop_bytes(pl.cfg, kTileBwdKey));
   pl.off_qaop = pl.off_bbop + align_up(nt * tile_bop_bytes(pl.cfg, d.dh, kTileBwdKey));
-  pl.off_qbop = pl.off_qaop + align_up(ntq * tile_aop_bytes(pl.cfg, kTileBwdQuery));
-  pl.off_zbar = pl.off_qbop + align_up(ntq * tile_bop_bytes(pl.cfg, d.dh, kTileBwdQuery));
+  pl.off_qbop = pl.off_qaop + align_up(nt * tile_aop_bytes(pl.cfg, kTileBwdQuery));
+  pl.off_zbar = pl.off_qbop + align_up(nt * tile_bop_bytes(pl.cfg, d.dh, kTileBwdQuery));
   pl.off_apart = pl.off_zbar + (pl.affine ? align_up(tokd) : 0);
   const long nb = (d.T + kAffineTokBlock - 1) / kAffineTokBlock;
   pl.scratch_bytes =
@@ -281,6 +278,15 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool saving, bool chain
   pl.off_sync = pl.off_carry + align_up(chk);
   if (pl.tile) {
     tile_plan(d, pl, tok, chk);
+    if (saving) {
+      // a scratch for long chunks serves chunks of 64 tokens too, up to 64 MB
+      e2ttt_desc d64 = d;
+      d64.chunk = 64;
+      Plan p64;
+      if (make_plan(&d64, p64, true) == E2TTT_OK)
+        pl.scratch_bytes =
+            std::max(pl.scratch_bytes, std::min(p64.scratch_bytes + kAlign, (size_t)64 << 20));
+    }
     return E2TTT_OK;
   }
   const long ns = pl.cfg.ns;
@@ -786,7 +792,6 @@ e2ttt_status e2ttt_chunk_backward_ln(const e2ttt_desc* desc, const float* ln_wei
     a.bops = at<char>(scratch, pl.off_bbop);
     a.qaops = at<char>(scratch, pl.off_qaop);
     a.qbops = at<char>(scratch, pl.off_qbop);
-    a.qall = pl.qall ? 1 : 0;
     a.ln_zbar = pl.affine ? at<float>(scratch, pl.off_zbar) : nullptr;
     a.U = pl.U; a.P = pl.P;
     a.copy = pl.copy; a.wunit = pl.wunit; a.wslot = pl.wslot; a.mslot = pl.mslot;

@@ -577,7 +577,7 @@ template <class G>
 __global__ void __launch_bounds__(256, 1) tile_bwd_token_kernel(TileBwdArgs a) {
   __shared__ BwdTileSmem<G> sm;
   static_assert(sizeof(BwdTileSmem<G>) <= 160 * 1024, "LDS budget");
-  const TileBlock b = tile_block(blockIdx.x, a.U, a.qall ? a.ntile : 2 * a.ntile);
+  const TileBlock b = tile_block(blockIdx.x, a.U, 2 * a.ntile);
   if (b.u >= a.U) return;
   const bool key = b.item < a.ntile;     // the key side takes longer and goes first
   const int tile = key ? b.item : b.item - a.ntile;
@@ -594,8 +594,11 @@ __global__ void __launch_bounds__(256, 1) tile_bwd_token_kernel(TileBwdArgs a) {
 }
 
 // The query side alone, of every chunk at once: none of it depends on the
-// adjoint state.  Ahead of a chain that leaves it out (chain_bwd.hip, QOFF), and
-// of the chunks' token kernels where one chunk's tiles do not fill the device.
+// adjoint state.  Ahead of a chain that leaves it out (chain_bwd.hip, QOFF).  (Not
+// ahead of the token kernels: with up to 128 tiles a chunk their query sides run
+// beside the key sides at no cost, and a launch of their own made the backward's
+// training step 2 to 14 % slower; with more tiles it gained 2 to 4 %, for memory
+// that grows with the sequence.)
 template <class G>
 __global__ void __launch_bounds__(256, 1) tile_bwd_query_kernel(TileBwdArgs a) {
   __shared__ BwdQuerySmem<G> sm;
@@ -673,7 +676,6 @@ __global__ void __launch_bounds__(256, G::FW == 0 || G::D == 64 ? 2 : 1)
     const float* car = a.carry + (u * a.NC + a.r) * 3;
     const float cw = car[0], cm = car[1], cb = car[2];
     const long tk = u * a.ntile_max;                            // the chunk's tiles
-    const long tq = a.qall ? (u * a.NC + a.r) * a.ntile_max : tk;
     // B operands BD tiles ahead (as many as two workgroups per CU leave
     // registers for), A operands two (one in flight, one in LDS)
     struct Stage {
@@ -686,7 +688,7 @@ __global__ void __launch_bounds__(256, G::FW == 0 || G::D == 64 ? 2 : 1)
         const int e = tid + v * 256, x = e / (IH * 64), o = e % (IH * 64);
         const char* src = x < G::NA_KEY
                               ? a.aops + ((tk + tile) * G::NA_KEY + x) * (G::NIB * 1024)
-                              : a.qaops + ((tq + tile) * G::NA_QRY + x - G::NA_KEY) * (G::NIB * 1024);
+                              : a.qaops + ((tk + tile) * G::NA_QRY + x - G::NA_KEY) * (G::NIB * 1024);
         if (e < NA * IH * 64) p.v[v] = reinterpret_cast<const u32x4*>(src)[ib0 * 64 + o];
       }
     };
@@ -698,7 +700,7 @@ __global__ void __launch_bounds__(256, G::FW == 0 || G::D == 64 ? 2 : 1)
       for (int x = 0; x < NB; ++x) {
         const char* src = x < G::NB_KEY
                               ? a.bops + ((tk + tile) * G::NB_KEY + x) * (njb * 1024L)
-                              : a.qbops + ((tq + tile) * G::NB_QRY + x - G::NB_KEY) * (njb * 1024L);
+                              : a.qbops + ((tk + tile) * G::NB_QRY + x - G::NB_KEY) * (njb * 1024L);
         f[x] = ld_frag(src, mine ? jb : 0, lane);
       }
     };
@@ -852,16 +854,12 @@ hipError_t run(const TileBwdArgs& base, hipStream_t s) {
   a.r = a.NC - 1;
   hipLaunchKernelGGL(tile_bwd_state_kernel<StateShape<G>>, dim3((unsigned)gs), dim3(256), 0, s, a);
   a.init = 0;
-  if (a.qall)
-    hipLaunchKernelGGL(tile_bwd_query_kernel<G>, dim3((unsigned)tile_grid(a.U, a.NC * a.ntile_max)),
-                       dim3(256), 0, s, a);
   for (int r = a.NC - 1; r >= 0; --r) {
     a.r = r;
     a.last = r == 0;
     a.ntile = (std::min(a.C, a.T - r * a.C) + kTileTok - 1) / kTileTok;
     hipLaunchKernelGGL(tile_bwd_token_kernel<G>,
-                       dim3((unsigned)tile_grid(a.U, a.qall ? a.ntile : 2 * a.ntile)), dim3(256), 0,
-                       s, a);
+                       dim3((unsigned)tile_grid(a.U, 2 * a.ntile)), dim3(256), 0, s, a);
     hipLaunchKernelGGL(tile_bwd_state_kernel<StateShape<G>>, dim3((unsigned)gs), dim3(256), 0, s,
                        a);
   }

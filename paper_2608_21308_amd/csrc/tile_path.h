@@ -69,9 +69,8 @@ struct TileBwdArgs {
   char* gops;           // [U][R of Wb | T of Wb | R of Mb | T of Mb]
   char* aops;           // key side: [U][ntile_max][dY, Yh, K], [A, dAh, Hh..]
   char* bops;
-  char* qaops;          // query side: [U][NC or 1][ntile_max][Yb_Q, Q], [A_Q, Hb_Q..]
-  char* qbops;
-  int qall;             // 1: of every chunk, formed by one launch ahead
+  char* qaops;          // query side: [U][ntile_max][Yb_Q, Q], [A_Q, Hb_Q..] (ahead of a
+  char* qbops;          // chain [U][NC][ntile_max])
   float* ln_zbar;       // with the affine: adjoint of a e
   long U, P, copy, wunit, wslot, mslot;
   int T, C, NC, dh, ntile_max;
