@@ -112,6 +112,11 @@ e2ttt_status select_config(const e2ttt_desc& d, ChainConfig& cfg) {
 
 constexpr int kTileRows = 32;   // tokens of a tile of that path
 
+// What a saving call may keep beside the chain's own memory so that it is faster
+// (operand copies of every chunk; operands of the query side in the backward's
+// scratch): longer sequences take the chain as it is.
+constexpr size_t kSavedBytes = (size_t)16 << 30;
+
 size_t tile_copy_bytes(const e2ttt_desc& d) {
   return (size_t)(d.fw == E2TTT_FW_GELU_MLP ? 2 : 3) * ((d.dh + 31) / 32 * 32) * d.d * 2;
 }
@@ -278,6 +283,14 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool saving, bool chain
   pl.off_sync = pl.off_carry + align_up(chk);
   if (pl.tile) {
     tile_plan(d, pl, tok, chk);
+    if (saving && (size_t)pl.NC * (pl.wslot + pl.mslot) > kSavedBytes) {
+      Plan chain;   // (at C = 512 the chain's saved activations are the larger part)
+      make_plan(desc, chain, true, true);
+      if (pl.ws_bytes_save + pl.scratch_bytes > chain.ws_bytes_save + chain.scratch_bytes)
+        pl.tile = false;
+    }
+  }
+  if (pl.tile) {
     if (saving) {
       // a scratch for long chunks serves chunks of 64 tokens too, up to 64 MB
       e2ttt_desc d64 = d;
@@ -314,8 +327,13 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool saving, bool chain
   pl.wunit = 3 * pl.copy;
   pl.wslot = (long)U * pl.wunit;
   // saving keeps every chunk's copies, for SwiGLU twice the memory of the chain
-  // alone: not above 16 GiB of them, so that the longest sequences still fit
-  pl.qoff = pl.qoff0 && pl.NC <= (16L << 30) / pl.wslot;
+  // alone, and the backward's scratch the query side's operands of every 32-token
+  // tile (Yb_Q, Q and A_Q, Hb_Q)
+  pl.ntile_max = (std::min(d.chunk, d.T) + kTileRows - 1) / kTileRows;
+  const long nmat = d.fw == E2TTT_FW_GELU_MLP ? 2 : 3;
+  const size_t nt = (size_t)U * pl.NC * pl.ntile_max, njb = (d.dh + 31) / 32 * 2;
+  const size_t qa_bytes = nt * 2 * (d.d / 16) * 1024, qb_bytes = nt * nmat * njb * 1024;
+  pl.qoff = pl.qoff0 && (size_t)pl.NC * pl.wslot <= kSavedBytes && qa_bytes + qb_bytes <= kSavedBytes;
   // without saving the query side needs the first layer's R copies and the second
   // layer's T copy only, of the chunks of one launch.  Each further launch costs
   // 28 us for the chain's start and end and its query sides, and 17 us more when
@@ -327,11 +345,9 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool saving, bool chain
   // launches (SwiGLU with up to 8 units three: a third more per copy), whose copies
   // stay below the backward's operands of the query side and, so that longer chunks
   // never need less, below a call's with chunks of 512
-  const long nmat = d.fw == E2TTT_FW_GELU_MLP ? 2 : 3;
   pl.copy0 = pl.copy / nmat * (nmat - 1);
   pl.wunit0 = 2 * pl.copy0 + pl.copy / nmat;
   const long wslot0 = (long)U * pl.wunit0;
-  pl.ntile_max = (std::min(d.chunk, d.T) + kTileRows - 1) / kTileRows;
   const long fit = (256L << 20) / wslot0;
   const long runs = nmat == 3 && pl.U <= 8 ? 3 : 2;
   pl.nslot = (int)std::min(
@@ -376,10 +392,8 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool saving, bool chain
   pl.off_bnx = pl.off_rbar + (pl.post_norm ? align_up((size_t)U * ns * pl.nrows * sizeof(float)) : 0);
   pl.off_qaop =
       pl.off_bnx + (pl.post_norm ? align_up(ngroups * ns * 2 * d.d * sizeof(float)) : 0);
-  // query-side operands of every 32-token tile: Yb_Q, Q and A_Q, Hb_Q
-  const size_t nt = (size_t)U * pl.NC * pl.ntile_max, njb = (d.dh + 31) / 32 * 2;
-  pl.off_qbop = pl.off_qaop + (pl.qoff ? align_up(nt * 2 * (d.d / 16) * 1024) : 0);
-  pl.scratch_bytes = pl.off_qbop + (pl.qoff ? align_up(nt * nmat * njb * 1024) : 0);
+  pl.off_qbop = pl.off_qaop + (pl.qoff ? align_up(qa_bytes) : 0);
+  pl.scratch_bytes = pl.off_qbop + (pl.qoff ? align_up(qb_bytes) : 0);
   return E2TTT_OK;
 }
 

@@ -1,10 +1,14 @@
 """Workspace sizes of the chains that leave the query side out (CPU): operand
 copies of every chunk are saved up to 16 GiB of them; above, a saving call's
 workspace and scratch are the chain's own again, while a call without saving
-keeps a bounded number of chunks' copies."""
+keeps a bounded number of chunks' copies.  The same bound for the token-tiled
+path, and for the operands in the backward's scratch."""
+import dataclasses
+
 import pytest
 
 from paper_2608_21308_amd import e2ttt
+from tests.path_util import takes_tiles
 
 GIB = 1 << 30
 
@@ -45,3 +49,24 @@ def test_one_launch_where_a_second_would_cost_more(fw, dh, U, NC):
 def test_few_units_and_many_chunks_need_no_more_than_the_backward(fw, dh, U, NC):
     free, _, scratch = sizes(fw, dh, U, 64 * NC)
     assert free <= scratch and free <= (256 << 20) + NC * 64 * U * 64
+
+
+def need(cfg):
+    return e2ttt.workspace_bytes(cfg, True) + e2ttt.backward_scratch_bytes(cfg)
+
+
+@pytest.mark.parametrize("fw,d,dh,U,T,C", [(0, 128, 512, 4, 20, 512), (0, 64, 256, 4, 20, 512),
+                                           (1, 64, 172, 8, 20, 512), (0, 128, 512, 8, 18, 65),
+                                           (0, 64, 120, 16, 21, 80), (1, 128, 344, 2, 20, 72),
+                                           (0, 64, 120, 64, 19, 512), (0, 64, 120, 2, 17, 1)])
+@pytest.mark.parametrize("flags", [0, e2ttt.FLAG_POST_NORM])
+def test_long_sequences_need_little_more_than_on_the_chain(fw, d, dh, U, T, C, flags):
+    cfg = e2ttt.Config(B=1, H=U, T=1 << T, d=d, dh=dh, chunk=C, fw=fw, io=e2ttt.DT_BF16, flags=flags)
+    # the chain's saved state in the operand type, LayerNorm rows and (MLP) the
+    # query side's activations and derivatives, as of one chunk of the bare chain:
+    # too few chunks to leave the query side out, too short for the token-tiled path
+    few = dataclasses.replace(cfg, T=4 * C, flags=cfg.flags | e2ttt.FLAG_POST_NORM)
+    chain = need(few) * (cfg.n_chunks / 4.0)
+    assert need(cfg) <= max(1.1 * chain, 33 * GIB)
+    if takes_tiles(cfg, True):      # its scratch: one chunk's operands, 64 MB, the scalar kernels'
+        assert e2ttt.backward_scratch_bytes(cfg) <= GIB // 8 + 16 * U * cfg.T
