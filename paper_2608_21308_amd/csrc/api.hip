@@ -286,8 +286,10 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool saving, bool chain
     if (saving && (size_t)pl.NC * (pl.wslot + pl.mslot) > kSavedBytes) {
       Plan chain;   // (at C = 512 the chain's saved activations are the larger part)
       make_plan(desc, chain, true, true);
-      if (pl.ws_bytes_save + pl.scratch_bytes > chain.ws_bytes_save + chain.scratch_bytes)
-        pl.tile = false;
+      if (pl.ws_bytes_save + pl.scratch_bytes > chain.ws_bytes_save + chain.scratch_bytes) {
+        pl = chain;
+        return E2TTT_OK;
+      }
     }
   }
   if (pl.tile) {

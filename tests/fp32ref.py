@@ -59,10 +59,12 @@ def scalar_kernels(eta, beta, gamma):
 
 
 def closed_form_unit(q, k, v, eta, beta, gamma, w_in, m_in, C, d, dh, fw, resln=True, eps=1e-5,
-                     ln_a=None, ln_b=None, post_norm=False):
+                     ln_a=None, ln_b=None, post_norm=False, saved=None):
     """One unit over all chunks: (outputs [T, d], W_T, M_T), differentiable;
     ln_a, ln_b: the unit's LayerNorm affine [d], or None; post_norm: the rows
-    rescaled to w_in's row norms at every chunk end."""
+    rescaled to w_in's row norms at every chunk end; saved: the form in which the
+    chunk-start states are kept (the net is evaluated at saved(W_0), the carries'
+    adjoints at saved(W_0) and saved(M_0); the carried values stay whole)."""
     T = q.shape[0]
     W = w_in
     M = m_in if m_in is not None else torch.zeros_like(w_in)
@@ -72,15 +74,20 @@ def closed_form_unit(q, k, v, eta, beta, gamma, w_in, m_in, C, d, dh, fw, resln=
         W0, M0 = W, M
         if not W0.requires_grad:
             W0 = W0.detach().requires_grad_(True)
+        Wn = W0 if saved is None else W0 + (saved(W0) - W0).detach()
         g = None if gamma is None else gamma[sl]
         kw, km, (cw, cm, cb) = scalar_kernels(eta[sl], beta[sl], g)
-        outs.append(torchref.net(W0, q[sl], d, dh, fw, resln, eps, ln_a, ln_b))
-        per_tok = 0.5 * ((torchref.net(W0, k[sl], d, dh, fw, resln, eps, ln_a, ln_b) - v[sl]) ** 2
+        outs.append(torchref.net(Wn, q[sl], d, dh, fw, resln, eps, ln_a, ln_b))
+        per_tok = 0.5 * ((torchref.net(Wn, k[sl], d, dh, fw, resln, eps, ln_a, ln_b) - v[sl]) ** 2
                          ).sum(-1)
         (gw,) = torch.autograd.grad((kw * per_tok).sum(), W0, create_graph=True)
         (gm,) = torch.autograd.grad((km * per_tok).sum(), W0, create_graph=True)
         W = cw * W0 + cm * M0 - gw
         M = cb * M0 - gm
+        if saved is not None:
+            dW, dM = (saved(W0) - W0).detach(), (saved(M0) - M0).detach()
+            W = W + (cw - cw.detach()) * dW + (cm - cm.detach()) * dM
+            M = M + (cb - cb.detach()) * dM
         if post_norm:
             W = torchref.row_normalise(W, w_in, d, dh, fw)
     return torch.cat(outs), W, M
@@ -114,7 +121,7 @@ def forward(x, *, C, fw, dh, flags=0, eps=1e-5, dtype=torch.float32, ln=None):
             np.stack(ms).reshape(B, H, P))
 
 
-def backward(x, *, C, fw, dh, flags=0, eps=1e-5, dtype=torch.float32, ln=None):
+def backward(x, *, C, fw, dh, flags=0, eps=1e-5, dtype=torch.float32, ln=None, saved=None):
     """Gradients of sum<d_out,out> + <d_w_out,w_out> + <d_m_out,m_out>, named as
     the oracle's (dq, dk, dv, d_eta, d_beta, d_gamma, d_w_in, d_m_in, and with
     the affine ln = (a, b) [H, d] also d_ln_a, d_ln_b summed over the batch),
@@ -144,7 +151,7 @@ def backward(x, *, C, fw, dh, flags=0, eps=1e-5, dtype=torch.float32, ln=None):
                                        C, d, dh, fw, resln, eps,
                                        None if ln is None else ta[h],
                                        None if ln is None else tb[h],
-                                       post_norm=bool(flags & 8))
+                                       post_norm=bool(flags & 8), saved=saved)
             loss = (o * _t(x["d_out"][b, h], dtype)).sum()
             if x.get("d_w_out") is not None:
                 loss = loss + (W * _t(x["d_w_out"][b, h], dtype)).sum()
@@ -176,3 +183,16 @@ def fp32_bar(err32: dict, tol: float = 1e-5) -> dict:
     err32 holds the float32 evaluation's errors under the same names as the
     GPU's (gpu_util.parity_errors: whole tensors and their local maxima)."""
     return {n: max(tol, FP32_FACTOR * e) for n, e in err32.items()}
+
+
+def bf16_state_bar(errors, x, ref, *, C, fw, dh, flags=0, ln=None, tol=2e-2):
+    """Bars of the gate gradients of a bf16 case: `tol`, or twice what a float64
+    evaluation reaches whose only rounding is that of the chunk-start states to
+    bf16, in which they are kept and multiplied, where that is larger: <Wb_C, W_0>
+    and its kin can cancel to a small part of their terms.  errors(got, ref, x, C):
+    the comparison the test makes; x, ref: its inputs and reference (a few units
+    will do)."""
+    got = backward(x, C=C, fw=fw, dh=dh, flags=flags, dtype=torch.float64, ln=ln,
+                   saved=lambda s: s.to(torch.bfloat16).to(s.dtype))
+    gates = {n: ref[n] for n in ("d_beta", "d_gamma") if ref.get(n) is not None}
+    return {n: max(tol, 2.0 * e) for n, e in errors(got, gates, x, C).items()}

@@ -128,9 +128,8 @@ def test_long_chunk_1p3b_layer_sampled_units():
                                           (300, 100, 64, 1), (700, 512, 172, 0),
                                           (260, 128, 64, 0)])
 def test_long_chunk_forward_swiglu_bf16(T, C, dh, flags):
-    # SwiGLU on bf16 re-forms W_0's operands at every product, so a long
-    # chunk's later tiles read W_0 from the copy the first tile stored; dh
-    # 64 / 128 / 172 run on one, two and three workgroups per unit
+    # (units so few take the token-tiled path; the chain kernels' long chunks on
+    # bf16 are in test_gpu_chain_long_chunks.py)
     w = WL.WORKLOADS[2].with_(B=2, H=2, T=T, C=C, dh=dh, backward=False, seed=1500 + T + dh)
     x = WL.make_inputs(w, with_grads=False)
     errs = errors(run_forward(w, x, flags), oracle_forward(w, x, flags), x, C)
