@@ -55,10 +55,9 @@
  * 1 <= chunk <= 512 (the paper's C = 512), forward and backward; a chunk
  * longer than the kernels' token tile (64 rows, 32 at d = 128) runs as
  * tiles that all take gradients and outputs at the chunk-start weights (one
- * after the other, or, where that is faster, all at once by plain launches
- * per chunk); e2ttt_apply takes d <= 64; T >= 1 with
- * a ragged last chunk of T mod chunk tokens allowed (Prop. 1 holds for any
- * chunk length).
+ * after the other, or, where that is faster, all at once by two launches
+ * per chunk); T >= 1 with a ragged last chunk of T mod chunk tokens allowed
+ * (Prop. 1 holds for any chunk length).
  * bf16 tensors use MFMA bf16 operands with fp32 accumulation and fp32 state;
  * f32 tensors use fp32 MFMA throughout.  Anything else returns
  * E2TTT_ERR_UNSUPPORTED.
@@ -144,9 +143,12 @@ size_t e2ttt_param_count(const e2ttt_desc* desc);
  * save_for_backward != 0 the workspace also keeps what the backward reuses
  * (per-token scalar kernels, chunk-start checkpoints of W and M in the
  * operand precision, the LayerNorm outputs and inverse deviations of the key
- * and query passes, and for the GELU MLP the query-side activations and GELU
- * derivatives), and the same buffer, untouched, must then be passed to
- * e2ttt_chunk_backward.  Returns 0 for a bad descriptor. */
+ * and query passes, and either every chunk's W in the orders in which the
+ * kernels multiply by it or, for the GELU MLP, the query-side activations and
+ * GELU derivatives; the former, of up to 16 GiB, where that is faster), and the
+ * same buffer, untouched, must then be passed to e2ttt_chunk_backward.  A
+ * workspace of that size also serves calls that do not save.  Returns 0 for a
+ * bad descriptor. */
 size_t e2ttt_workspace_bytes(const e2ttt_desc* desc, int save_for_backward);
 
 /* Bytes of `scratch` that e2ttt_chunk_backward needs (0 for a bad descriptor). */
@@ -288,8 +290,9 @@ e2ttt_status e2ttt_wait_status(const e2ttt_desc* desc, const void* workspace,
  * e2ttt_chunk_forward with save_for_backward = 0 on a workspace the library
  * owns, a device array of E2TTT_STATIC_WORKSPACE_BYTES on each GPU it runs
  * on, held until the process ends.  Inputs, outputs and their rules are those
- * of e2ttt_chunk_forward.  A descriptor whose workspace
- * (e2ttt_workspace_bytes(desc, 0)) exceeds E2TTT_STATIC_WORKSPACE_BYTES
+ * of e2ttt_chunk_forward.  Where the faster kernels' workspace
+ * (e2ttt_workspace_bytes(desc, 0)) exceeds E2TTT_STATIC_WORKSPACE_BYTES, the
+ * call runs on those that need least; a descriptor too large for them as well
  * returns E2TTT_ERR_WORKSPACE_TOO_SMALL before anything is launched.  The call
  * allocates nothing.  Every call on a GPU shares that GPU's array: calls that
  * overlap on one GPU race (enqueue them on one stream, or wait between them).

@@ -110,8 +110,6 @@ e2ttt_status select_config(const e2ttt_desc& d, ChainConfig& cfg) {
   return E2TTT_OK;
 }
 
-constexpr int kTileRows = 32;   // tokens of a tile of that path
-
 // What a saving call may keep beside the chain's own memory so that it is faster
 // (operand copies of every chunk; operands of the query side in the backward's
 // scratch): longer sequences take the chain as it is.
@@ -127,14 +125,16 @@ size_t tile_copy_bytes(const e2ttt_desc& d) {
 // chunk's time on the few CUs it uses; apart they use the whole device, but W_0
 // goes through memory as operand copies.  Time of the chain alone over this,
 // head dim 64, C = 64 (C = 16 alike), 8 / 32 / 128 chunks:
-//   forward  MLP 256:    8 units 1.11 1.12 1.19, 32 units 1.06 1.05, 64 units 0.99 0.98
-//            MLP 120:    1.13 1.15 1.23, 1.10 1.11, 64 units 1.07 1.05
-//            SwiGLU 172: 1.15 1.10 1.22, 1.11 1.03, 64 units 1.02 0.95
-//            SwiGLU 64:  1.14 1.09 1.22, 1.11 1.05, 64 units 1.07 0.99
-//   training MLP 256:    1.10 1.16, 1.06 1.09, 64 units 0.98 0.99
-//   step     MLP 120:    1.05 1.18 1.18, 1.08 1.14, 64 units 1.04 1.07
-//            SwiGLU 172: 1.14 1.20 1.20, 1.09 1.13, 64 units 1.03 1.03
-// and with 4 chunks 0.96 to 1.07 (the launches).
+//   forward  MLP 256:    8 units 1.08 1.04 1.17, 32 units 1.05 1.12 1.10
+//            MLP 120:    1.15 1.17 1.25, 1.12 1.19 1.21, 64 units 1.07 1.13 1.12
+//            SwiGLU 172: 1.13 1.00 1.19, 1.10 1.17 1.15
+//            SwiGLU 64:  1.16 1.10 1.23, 1.13 1.20 1.22
+//   training MLP 256:    1.07 1.15 1.16, 1.04 1.08 1.08
+//   step     MLP 120:    1.14 1.18 1.20, 1.10 1.13 1.14, 64 units 1.06 1.08 1.07
+//            SwiGLU 172: 1.13 1.19 1.21, 1.09 1.14 1.14
+//            SwiGLU 64:  1.17 1.21 1.23, 1.12 1.17 1.18
+// The nets left out above 32 units reached 0.95 to 1.07 with 64 (forward in several
+// launches), all of them 0.96 to 1.07 with 4 chunks (the launches).
 bool leaves_query(const e2ttt_desc& d, const Plan& pl) {
   const bool mlp = d.fw == E2TTT_FW_GELU_MLP;
   if (!pl.cfg.bf || d.d != 64 || pl.NC < 8) return false;
@@ -199,7 +199,7 @@ bool takes_tiles(const e2ttt_desc& d, const Plan& pl, bool saving) {
   const int whole = d.T / d.chunk, rest = d.T % d.chunk;
   for (int k = 0; k < 2; ++k) {
     const int len = k == 0 ? d.chunk : rest, n = k == 0 ? whole : (rest > 0 ? 1 : 0);
-    const int nt = (len + kTileRows - 1) / kTileRows;
+    const int nt = (len + kTileTok - 1) / kTileTok;
     tiles_us += n * (waves(units * 2 * nt) * (t.tok + t.tokq * quarters) +
                      units * 2 * nt / 256 * t.tokb * blocks + state_waves * (t.st + t.stn * nt));
     chain_us += n * ((len + rows - 1) / rows) * chain_tile;
@@ -216,7 +216,7 @@ void tile_plan(const e2ttt_desc& d, Plan& pl, size_t tok, size_t chk) {
   pl.wunit = 3 * pl.copy;
   pl.wslot = (long)U * pl.wunit;
   pl.mslot = (long)U * pl.copy;
-  pl.ntile_max = (std::min(d.chunk, d.T) + kTileRows - 1) / kTileRows;
+  pl.ntile_max = (std::min(d.chunk, d.T) + kTileTok - 1) / kTileTok;
   // (the status word of a call on the chain, which the other kind of call may be)
   pl.off_state = pl.off_sync + kAlign;
   pl.off_aop = pl.off_state + align_up(U * 4 * pl.copy);   // W and M, fp32
@@ -331,7 +331,7 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool saving, bool chain
   // saving keeps every chunk's copies, for SwiGLU twice the memory of the chain
   // alone, and the backward's scratch the query side's operands of every 32-token
   // tile (Yb_Q, Q and A_Q, Hb_Q)
-  pl.ntile_max = (std::min(d.chunk, d.T) + kTileRows - 1) / kTileRows;
+  pl.ntile_max = (std::min(d.chunk, d.T) + kTileTok - 1) / kTileTok;
   const long nmat = d.fw == E2TTT_FW_GELU_MLP ? 2 : 3;
   const size_t nt = (size_t)U * pl.NC * pl.ntile_max, njb = (d.dh + 31) / 32 * 2;
   const size_t qa_bytes = nt * 2 * (d.d / 16) * 1024, qb_bytes = nt * nmat * njb * 1024;

@@ -52,7 +52,7 @@ extern "C" e2ttt_status e2ttt_chunk_forward_static(const e2ttt_desc* desc, const
   if (need == 0)   // a bad descriptor: the forward reports which check failed
     return e2ttt_chunk_forward(desc, q, k, v, eta, beta, gamma, w_in, m_in, out, w_out, m_out,
                                nullptr, 0, 0, stream);
-  // long chunks whose token-tiled path needs more run on the chain kernels
+  // calls whose token-tiled path or operand copies need more run on the chain alone
   const bool chain = need > E2TTT_STATIC_WORKSPACE_BYTES;
   if (chain && e2ttt::chain_workspace_bytes(desc) > E2TTT_STATIC_WORKSPACE_BYTES)
     return E2TTT_ERR_WORKSPACE_TOO_SMALL;

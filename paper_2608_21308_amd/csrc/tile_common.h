@@ -37,10 +37,9 @@
 #pragma once
 
 #include "chain_common.h"
+#include "tile_path.h"
 
 namespace e2ttt {
-
-constexpr int kTileTok = 32;   // tokens of a tile (one K-step of the state sums)
 
 template <int FW_, int D_, int MAXQ_>
 struct TileShape {
@@ -316,10 +315,5 @@ struct FragRing {
     return r;
   }
 };
-
-// Bytes of one operand copy of all matrices of a unit.
-__host__ __device__ inline long tile_copy_bytes(int nmat, int d, int dh) {
-  return (long)nmat * ((dh + 31) / 32 * 32) * d * 2;
-}
 
 }  // namespace e2ttt

@@ -380,7 +380,6 @@ template <class G>
 __global__ void __launch_bounds__(256, 1) tile_fwd_state_kernel(TileFwdArgs a) {
   constexpr int D = G::D, IH = G::IH, NMAT = G::NMAT, NF = G::NF, SEC = G::SEC;
   constexpr int NA = G::NA_FWD;
-  constexpr int BD = 3;
   constexpr int NV = (NA * IH * 64 + 255) / 256;   // staged 16-byte vectors per thread
   __shared__ __attribute__((aligned(16))) u32x4 sa[2][NA * IH * 64];
   __shared__ __attribute__((aligned(16))) float sk[2][2][kTileTok];
@@ -433,8 +432,7 @@ __global__ void __launch_bounds__(256, 1) tile_fwd_state_kernel(TileFwdArgs a) {
     const int s0 = a.r * a.C, L = min(a.C, a.T - s0);
     const char* const aop = a.aops + u * a.ntile_max * (long)NA * G::NIB * 1024;
     const char* const bop = a.bops + u * a.ntile_max * (long)G::NB_FWD * njb * 1024;
-    // B operands BD tiles ahead (as many as two workgroups per CU leave
-    // registers for), A operands and scalars two (one in flight,
+    // B operands three tiles ahead, A operands and scalars two (one in flight,
     // one in LDS): a step is some 500 cycles, a load from memory several times that
     struct Stage {
       u32x4 v[NV];
@@ -463,10 +461,8 @@ __global__ void __launch_bounds__(256, 1) tile_fwd_state_kernel(TileFwdArgs a) {
     load_a(p0, 0);
     load_b(b0, 0);
     load_a(p1, 1);
-    if constexpr (BD == 3) {
-      load_b(b1, 1);
-      load_b(b2, 2);
-    }
+    load_b(b1, 1);
+    load_b(b2, 2);
 #pragma unroll
     for (int m = 0; m < NMAT; ++m)
 #pragma unroll
@@ -483,7 +479,7 @@ __global__ void __launch_bounds__(256, 1) tile_fwd_state_kernel(TileFwdArgs a) {
       if (tid < 64) sk[par][tid >> 5][tid & 31] = p.k;
       __syncthreads();
       load_a(p, tile + 2);
-      load_b(later, tile + BD);
+      load_b(later, tile + 3);
       pin_loads();
       const bf16x8* sf = reinterpret_cast<const bf16x8*>(sa[par]);
       if constexpr (G::FW == 0) {
@@ -532,18 +528,11 @@ __global__ void __launch_bounds__(256, 1) tile_fwd_state_kernel(TileFwdArgs a) {
       }
     };
     // (a tile's buffers are rewritten two steps later, after the next step's barrier)
-    if constexpr (BD == 3) {
-      for (int tile = 0; tile < a.ntile; tile += 4) {
-        step(tile, 0, p0, b0, b3);
-        step(tile + 1, 1, p1, b1, b0);
-        step(tile + 2, 0, p0, b2, b1);
-        step(tile + 3, 1, p1, b3, b2);
-      }
-    } else {
-      for (int tile = 0; tile < a.ntile; tile += 2) {
-        step(tile, 0, p0, b0, b1);
-        step(tile + 1, 1, p1, b1, b0);
-      }
+    for (int tile = 0; tile < a.ntile; tile += 4) {
+      step(tile, 0, p0, b0, b3);
+      step(tile + 1, 1, p1, b1, b0);
+      step(tile + 2, 0, p0, b2, b1);
+      step(tile + 3, 1, p1, b3, b2);
     }
   }
 

@@ -5,6 +5,8 @@
 
 namespace e2ttt {
 
+constexpr int kTileTok = 32;   // tokens of a tile (one K-step of the state sums)
+
 struct TileFwdArgs {
   const void* q;
   const void* k;
