@@ -175,17 +175,19 @@ double waves(double n) { return 0.5 * (std::ceil(n / 256) + std::max(1.0, n / 25
 // The constants are a least-squares fit to the times of 9,289 calls on the tiles
 // and 10,704 on the chain: both nets and head dims, every width, 1 to 520 units,
 // chunks of 65 to 512 tokens, up to fourteen chunks, the last one ragged; nine
-// tenths of the estimates of any net lie within 0.82 and 1.18 of the time.  With
-// the margin no timed call lost more than 4 % to the chain alone on the tiles (one
-// 5 % to a chain that leaves its query side out); without it 2 % of them did, the
-// worst by 11 %.  Chain over tiles, forward / step, head dim 64, dh 256, C = 128: 8
-// units 1.3 / 1.5, 128 units 0.5 / 0.6; C = 512: 2.9 / 3.1, 0.8 / 0.8; head dim
-// 128, dh 512, C = 128: 8 units 2.0 / 2.2, 128 units 1.5 / 1.6; dh 33, C = 68: 107
-// units 0.86 / 0.92.
+// tenths of the estimates of any net lie within 0.83 and 1.21 of the time.  Of
+// 8,316 calls timed on both paths the 7,653 that go to the tiles gained 2.0 in the
+// geometric mean and one lost (5 %, to a chain that leaves its query side out);
+// 107 of the others would have gained more than a tenth.  Without the margin 22
+// would have lost, by up to 8 %.  Chain over tiles, forward / step, head dim 64, dh
+// 256, C = 128: 8 units 1.3 / 1.5, 128 units 0.5 / 0.6; C = 512: 2.9 / 3.1, 0.8 /
+// 0.8; head dim 128, dh 512, C = 128: 8 units 2.0 / 2.2, 128 units 1.5 / 1.6; dh
+// 33, C = 68: 107 units 0.86 / 0.92.
 bool takes_tiles(const e2ttt_desc& d, const Plan& pl, bool saving) {
   const int rows = 16 * pl.cfg.ntb, ns = pl.cfg.ns;
-  // (at head dim 128 shorter chunks are left on the chain: their gain was 1.15 to
-  // 2.0 where this estimate took them, for twice the saved memory per token)
+  // (at head dim 128 chunks of 33 to 64 tokens are left on the chain, whose saved
+  // memory is half as much; where the tiles were estimated to be faster they were,
+  // by 1.15 to 2.0)
   if (!pl.cfg.bf || pl.post_norm || std::min(d.chunk, d.T) <= 64 || !tile_supported(pl.cfg, d.dh))
     return false;
   const PathTimes& t = kPathTimes[saving][d.fw == E2TTT_FW_SWIGLU][d.d == 128];
