@@ -114,6 +114,9 @@ e2ttt_status select_config(const e2ttt_desc& d, ChainConfig& cfg) {
 // (operand copies of every chunk; operands of the query side in the backward's
 // scratch): longer sequences take the chain as it is.
 constexpr size_t kSavedBytes = (size_t)16 << 30;
+// How much a buffer may be made larger so that it serves other calls as well: of
+// the same shape in shorter chunks, a backward's of a forward that does not save.
+constexpr size_t kServes = (size_t)64 << 20;
 
 size_t tile_copy_bytes(const e2ttt_desc& d) {
   return (size_t)(d.fw == E2TTT_FW_GELU_MLP ? 2 : 3) * ((d.dh + 31) / 32 * 32) * d.d * 2;
@@ -125,14 +128,14 @@ size_t tile_copy_bytes(const e2ttt_desc& d) {
 // chunk's time on the few CUs it uses; apart they use the whole device, but W_0
 // goes through memory as operand copies.  Time of the chain alone over this,
 // head dim 64, C = 64 (C = 16 alike), 8 / 32 / 128 chunks:
-//   forward  MLP 256:    8 units 1.08 1.04 1.17, 32 units 1.05 1.12 1.10
-//            MLP 120:    1.15 1.17 1.25, 1.12 1.19 1.21, 64 units 1.07 1.13 1.12
-//            SwiGLU 172: 1.13 1.00 1.19, 1.10 1.17 1.15
-//            SwiGLU 64:  1.16 1.10 1.23, 1.13 1.20 1.22
-//   training MLP 256:    1.07 1.15 1.16, 1.04 1.08 1.08
-//   step     MLP 120:    1.14 1.18 1.20, 1.10 1.13 1.14, 64 units 1.06 1.08 1.07
-//            SwiGLU 172: 1.13 1.19 1.21, 1.09 1.14 1.14
-//            SwiGLU 64:  1.17 1.21 1.23, 1.12 1.17 1.18
+//   forward  MLP 256:    8 units 1.08 1.18 1.21, 32 units 1.05 1.11 1.10
+//            MLP 120:    1.15 1.24 1.27, 1.12 1.18 1.21, 64 units 1.07 1.13 1.12
+//            SwiGLU 172: 1.12 1.24 1.26, 1.09 1.16 1.14
+//            SwiGLU 64:  1.16 1.25 1.27, 1.12 1.19 1.22
+//   training MLP 256:    1.06 1.15 1.16, 1.04 1.07 1.08
+//   step     MLP 120:    1.14 1.18 1.20, 1.09 1.14 1.14, 64 units 1.05 1.08 1.07
+//            SwiGLU 172: 1.13 1.19 1.21, 1.09 1.13 1.14
+//            SwiGLU 64:  1.17 1.21 1.23, 1.12 1.17 1.17
 // The nets left out above 32 units reached 0.95 to 1.07 with 64 (forward in several
 // launches), all of them 0.96 to 1.07 with 4 chunks (the launches).
 bool leaves_query(const e2ttt_desc& d, const Plan& pl) {
@@ -295,14 +298,16 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool saving, bool chain
     }
   }
   if (pl.tile) {
-    if (saving) {
-      // a scratch for long chunks serves chunks of 64 tokens too, up to 64 MB
-      e2ttt_desc d64 = d;
-      d64.chunk = 64;
-      Plan p64;
-      if (make_plan(&d64, p64, true) == E2TTT_OK)
-        pl.scratch_bytes =
-            std::max(pl.scratch_bytes, std::min(p64.scratch_bytes + kAlign, (size_t)64 << 20));
+    // a buffer for long chunks serves chunks of 64 tokens too
+    e2ttt_desc d64 = d;
+    d64.chunk = 64;
+    Plan p64;
+    if (make_plan(&d64, p64, saving) == E2TTT_OK) {
+      // (and the W_0 blocks that the chain would keep for long ones)
+      const size_t w0 = (size_t)std::max(p64.npairs * pl.cfg.ns, U) * chain_frz_floats(pl.cfg) * 4;
+      pl.ws_bytes = std::max(pl.ws_bytes, std::min(p64.ws_bytes + w0, kServes));
+      pl.ws_bytes_save = std::max(pl.ws_bytes_save, std::min(p64.ws_bytes_save + w0, kServes));
+      pl.scratch_bytes = std::max(pl.scratch_bytes, std::min(p64.scratch_bytes + kAlign, kServes));
     }
     return E2TTT_OK;
   }
@@ -339,23 +344,16 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool saving, bool chain
   const size_t qa_bytes = nt * 2 * (d.d / 16) * 1024, qb_bytes = nt * nmat * njb * 1024;
   pl.qoff = pl.qoff0 && (size_t)pl.NC * pl.wslot <= kSavedBytes && qa_bytes + qb_bytes <= kSavedBytes;
   // without saving the query side needs the first layer's R copies and the second
-  // layer's T copy only, of the chunks of one launch.  Each further launch costs
-  // 28 us for the chain's start and end and its query sides, and 17 us more when
-  // it is cooperative.  Gain over the chain alone in one / two / three launches:
-  // 13 chunks 1.08 to 1.16 / 0.84 to 0.88 (MLP 256), 0.92 (SwiGLU 172); 32 chunks,
-  // 8 to 16 units 1.15 to 1.20 / 1.03 to 1.06 / SwiGLU 1.00 to 0.97; 32 units 1.12
-  // to 1.16 / 0.98 to 1.03.  So calls below 32 chunks and those above 16 units take
-  // all chunks at once, in up to 256 MB (65 chunks or more).  The others take two
-  // launches (SwiGLU with up to 8 units three: a third more per copy), whose copies
-  // stay below the backward's operands of the query side and, so that longer chunks
-  // never need less, below a call's with chunks of 512
+  // layer's T copy only, of the chunks of one launch: as many as 256 MB hold (65 or
+  // more), since each further launch costs 28 us for the chain's start and end and
+  // its query sides, and 17 us more when it is cooperative.  Gain over the chain
+  // alone in one / two / three launches: 13 chunks 1.08 to 1.16 / 0.84 to 0.88 (MLP
+  // 256), 0.92 (SwiGLU 172); 32 chunks, 8 to 16 units 1.15 to 1.20 / 1.03 to 1.06 /
+  // SwiGLU 0.97 to 1.00; 32 units 1.12 to 1.16 / 0.98 to 1.03
   pl.copy0 = pl.copy / nmat * (nmat - 1);
   pl.wunit0 = 2 * pl.copy0 + pl.copy / nmat;
   const long wslot0 = (long)U * pl.wunit0;
-  const long fit = (256L << 20) / wslot0;
-  const long runs = nmat == 3 && pl.U <= 8 ? 3 : 2;
-  pl.nslot = (int)std::min(
-      pl.NC, pl.U > 16 ? fit : std::max(pl.NC < 32 ? 31L : 1L, std::min(fit, (pl.NC + runs - 1) / runs)));
+  pl.nslot = (int)std::min(pl.NC, (256L << 20) / wslot0);
   const long nrun = (pl.NC + pl.nslot - 1) / pl.nslot;
   pl.nslot = (int)((pl.NC + nrun - 1) / nrun);
   pl.off_wops0 = pl.off_ckpt;
@@ -398,6 +396,10 @@ e2ttt_status make_plan(const e2ttt_desc* desc, Plan& pl, bool saving, bool chain
       pl.off_bnx + (pl.post_norm ? align_up(ngroups * ns * 2 * d.d * sizeof(float)) : 0);
   pl.off_qbop = pl.off_qaop + (pl.qoff ? align_up(qa_bytes) : 0);
   pl.scratch_bytes = pl.off_qbop + (pl.qoff ? align_up(qb_bytes) : 0);
+  // (compared without what the options add: they add it either way)
+  const size_t own = pl.scratch_bytes - (pl.off_qaop - pl.off_zbar);
+  const size_t fwd = align_up(pl.ws_bytes - (pl.off_ckpt - pl.off_ntgt));
+  pl.scratch_bytes += std::max(own, std::min(fwd, kServes)) - own;
   return E2TTT_OK;
 }
 

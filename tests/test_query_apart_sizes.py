@@ -36,19 +36,28 @@ def slot_bytes(fw, dh, U):
     return U * (2 * (mats - 1) + 1) * ((dh + 31) // 32 * 32) * 64 * 2
 
 
-@pytest.mark.parametrize("fw,dh,U,NC", [(0, 256, 8, 13), (0, 256, 8, 31), (0, 256, 32, 64),
-                                        (1, 172, 16, 31), (0, 120, 64, 40)])
-def test_one_launch_where_a_second_would_cost_more(fw, dh, U, NC):
+@pytest.mark.parametrize("fw,dh,U,NC", [(0, 256, 8, 13), (0, 256, 8, 32), (0, 256, 32, 64),
+                                        (1, 172, 8, 64), (1, 172, 16, 128), (0, 120, 64, 40)])
+def test_one_launch_where_the_copies_fit(fw, dh, U, NC):
     # (a launch too many costs as much as the query sides of some twenty chunks)
     slot = slot_bytes(fw, dh, U)
     assert NC * slot <= 256 << 20
     assert sizes(fw, dh, U, 64 * NC)[0] - sizes(fw, dh, U, 64 * 8)[0] >= (NC - 8) * slot
 
 
-@pytest.mark.parametrize("fw,dh,U,NC", [(0, 256, 8, 32), (1, 172, 16, 128), (0, 256, 16, 512)])
-def test_few_units_and_many_chunks_need_no_more_than_the_backward(fw, dh, U, NC):
-    free, _, scratch = sizes(fw, dh, U, 64 * NC)
-    assert free <= scratch and free <= (256 << 20) + NC * 64 * U * 64
+@pytest.mark.parametrize("fw,dh,U", [(0, 256, 8), (1, 172, 16), (0, 120, 64), (1, 64, 2)])
+@pytest.mark.parametrize("T", [512, 2048, 8192])
+def test_buffers_serve_other_calls_up_to_64_mb(fw, dh, U, T):
+    # a backward's scratch a forward without saving; a buffer for long chunks the same
+    # tokens in chunks of 64
+    free, _, scratch = sizes(fw, dh, U, T)
+    assert scratch >= min(free, 64 << 20)
+    for C in (128, 512):
+        long = e2ttt.Config(B=1, H=U, T=T, d=64, dh=dh, chunk=C, fw=fw, io=e2ttt.DT_BF16)
+        if takes_tiles(long, False):
+            assert e2ttt.workspace_bytes(long, False) >= min(free, 64 << 20)
+        if takes_tiles(long, True):
+            assert e2ttt.backward_scratch_bytes(long) >= min(scratch, 64 << 20)
 
 
 def need(cfg):
