@@ -41,31 +41,40 @@ def test_concurrent_streams_equal_one_stream(fw, d, dh, C):
             assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("fw,d,dh,C", [(0, 64, 256, 64), (1, 64, 172, 64)])
+@pytest.mark.parametrize("fw,d,dh,C", [(0, 64, 256, 64), (1, 64, 172, 64), (0, 128, 512, 32)])
 def test_concurrent_graphs_equal_one_stream(fw, d, dh, C):
-    w = WL.WORKLOADS[1].with_(fw=fw, B=8, H=16, T=256, d=d, dh=dh, C=C, seed=4350 + dh)
+    # a training step captured per stream, the graphs replayed at once
+    w = WL.WORKLOADS[1].with_(fw=fw, B=8, H=16, T=256, d=d, dh=dh, C=C, backward=True,
+                              seed=4350 + dh)
     cfg = config_of(w)
-    t = to_dev(WL.make_inputs(w, with_grads=False), w.io)
+    t = to_dev(WL.make_inputs(w, with_grads=True), w.io)
     args = t["q"], t["k"], t["v"], t["eta"], t["beta"], t["gamma"], t["w_in"], None
-    ref = e2ttt.forward(cfg, *args)[:3]
+
+    def step(ws, scratch):
+        out, wo, mo, _ = e2ttt.forward(cfg, *args, workspace=ws, save_for_backward=True)
+        g = e2ttt.backward(cfg, *args, ws, t["d_out"], scratch=scratch)
+        return [out, wo, mo, *[g[n] for n in sorted(g)]]
+
+    def buffers():
+        return (e2ttt.alloc_workspace(cfg, True),
+                torch.empty(e2ttt.backward_scratch_bytes(cfg), dtype=torch.uint8, device="cuda"))
+
+    ref = step(*buffers())
     runs = []
     for _ in range(3):
-        s = torch.cuda.Stream()
-        got = [torch.empty_like(r) for r in ref]
-        ws = e2ttt.alloc_workspace(cfg, False)
-        graph = torch.cuda.CUDAGraph()
+        s, bufs, graph = torch.cuda.Stream(), buffers(), torch.cuda.CUDAGraph()
         torch.cuda.synchronize()
         with torch.cuda.graph(graph, stream=s):
-            e2ttt.forward(cfg, *args, out=got[0], w_out=got[1], m_out=got[2], workspace=ws)
-        runs.append((s, got, ws, graph))
+            got = step(*bufs)
+        runs.append((s, got, bufs, graph))
     for _ in range(3):
         for s, got, _, graph in runs:
             with torch.cuda.stream(s):
                 for g in got:
                     g.fill_(float("nan"))
                 graph.replay()
-        for s, got, ws, _ in runs:
+        for s, got, (ws, scratch), _ in runs:
             with torch.cuda.stream(s):
-                assert e2ttt.wait_status(cfg, ws) == 0
+                assert e2ttt.wait_status(cfg, ws, scratch) == 0
             for a, b in zip(got, ref):
                 assert torch.equal(a, b)

@@ -105,3 +105,31 @@ def test_saving_and_other_calls_on_different_paths_share_a_workspace():
         assert torch.equal(a, c)
         a, b = a.double(), b.double()
         assert float((a - b).norm()) <= 1e-2 * float(b.norm())
+
+
+def test_state_in_place_and_under_capture():
+    # w_out over w_in, m_out over m_in; and the launches of all chunks as one graph
+    w = WL.WORKLOADS[1].with_(fw=0, B=1, H=3, T=300, d=64, dh=256, C=97, seed=4270)
+    cfg = config_of(w)
+    assert takes_tiles(cfg, False)
+    x = with_state_inputs(WL.make_inputs(w, with_grads=False), 5, 1e-2, False)
+    t = to_dev(x, w.io)
+    args = t["q"], t["k"], t["v"], t["eta"], t["beta"], t["gamma"]
+    *ref, ws = e2ttt.forward(cfg, *args, t["w_in"], t["m_in"])
+    st = t["w_in"].clone(), t["m_in"].clone()
+    out = e2ttt.forward(cfg, *args, *st, w_out=st[0], m_out=st[1], workspace=ws)[0]
+    for n, a, b in zip(("out", "w_out", "m_out"), (out, *st), ref):
+        assert torch.equal(a, b), n
+    got = [torch.empty_like(r) for r in ref]
+    s, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=s):
+        e2ttt.forward(cfg, *args, t["w_in"], t["m_in"], out=got[0], w_out=got[1], m_out=got[2],
+                      workspace=ws)
+    for _ in range(3):
+        for g in got:
+            g.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        for n, a, b in zip(("out", "w_out", "m_out"), got, ref):
+            assert torch.equal(a, b), "graph: " + n
